@@ -157,7 +157,9 @@ typedef enum lift_lane_form {
  *      its rows; MD: n k; a batch: one bucket) -- a table built into the library from the autotuner's
  *      cache, used only on a device of the architecture and compute-unit
  *      count it was tuned on;
- *   3. else the library defaults.
+ *   3. else the library defaults (gemv: also where the tuned knobs' vector
+ *      loads do not fit A's row starts and x's alignment; its launch then
+ *      goes by row length, for any alignment, as it does for all-zero knobs).
  * lift_default_knobs reports which applies.  Explicit knobs are never
  * overridden. */
 typedef struct lift_knobs {
@@ -265,6 +267,17 @@ lift_status lift_dot_ex_noalloc(int64_t n, lift_dtype xt, const void *x, const v
 lift_status lift_gemv_ex(int64_t m, int64_t n, float alpha, lift_dtype at, const void *A,
                          int64_t lda, const float *x, float beta, float *y, lift_acc acc,
                          const lift_knobs *knobs, hipStream_t stream);
+
+/* lift_gemv_ex with a workspace (the one of asum / dot, under the same rules:
+ * zeroed once, left zeroed, one per set of calls that may run concurrently;
+ * LIFT_EWORKSPACE if null or too small, LIFT_EINVAL if misaligned or
+ * overlapping y).  With few, long rows (rows above 64 KiB, at most one row
+ * or pair of rows per compute unit) the library then splits each row over
+ * several work-groups, whose partials meet in the workspace in a fixed
+ * order; every other shape runs as lift_gemv_ex. */
+lift_status lift_gemv_ex_ws(int64_t m, int64_t n, float alpha, lift_dtype at, const void *A,
+                            int64_t lda, const float *x, float beta, float *y, lift_acc acc, void *ws,
+                            size_t ws_bytes, const lift_knobs *knobs, hipStream_t stream);
 
 /* ---- BlackScholes (Section 5.2) ----------------------------------------- */
 

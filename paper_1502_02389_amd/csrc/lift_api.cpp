@@ -474,6 +474,36 @@ const void *gemv_split_table(int dt, int acc, int vb, int rows, int unroll, bool
     }
 }
 
+const void *gemv_rows_table(int dt, int acc, int vb, int lanes, int v, int r)
+{
+    switch (dt) {
+    case LIFT_F32: return gemv_rows_kernel_f32(acc, vb, lanes, v, r);
+    case LIFT_BF16: return gemv_rows_kernel_bf16(acc, vb, lanes, v, r);
+    case LIFT_F16: return gemv_rows_kernel_f16(acc, vb, lanes, v, r);
+    default: return nullptr;
+    }
+}
+
+const void *gemv_rows_wg_table(int dt, int acc, int v)
+{
+    switch (dt) {
+    case LIFT_F32: return gemv_rows_wg_kernel_f32(acc, v);
+    case LIFT_BF16: return gemv_rows_wg_kernel_bf16(acc, v);
+    case LIFT_F16: return gemv_rows_wg_kernel_f16(acc, v);
+    default: return nullptr;
+    }
+}
+
+const void *gemv_panel_table(int dt, int acc, int r)
+{
+    switch (dt) {
+    case LIFT_F32: return gemv_panel_kernel_f32(acc, r);
+    case LIFT_BF16: return gemv_panel_kernel_bf16(acc, r);
+    case LIFT_F16: return gemv_panel_kernel_f16(acc, r);
+    default: return nullptr;
+    }
+}
+
 // Checks of a reduction's operands (everything but the workspace).
 lift_status reduce_check(int op, int64_t n, int xt, const void *x, const void *y, int acc, int rt,
                          const void *result)
@@ -584,9 +614,142 @@ lift_status reduce_common(int op, int64_t n, int xt, const void *x, const void *
     return launch(kern, grid, k.block, &a, stream);
 }
 
+// gemv whose launch is left to the library (no knobs and no tuned entry for
+// its shape and alignment, or all-zero knobs): the kernels of
+// lift_gemv_rows.hpp by row length.  n >= 1, m >= 1.  ws: a reduction
+// workspace, or null.
+//
+// Measured on MI355X (us, back to back, cold inputs; before = the launch the
+// library took until these kernels):
+//   rows (m x n)        storage  before    now
+//   1000000 x 33        f32      339       21
+//   65536 x 64          f32      27        4.7
+//   65536 x 257         bf16     28        10.5
+//   16384 x 1000        bf16     13.8      7.6
+//   20000 x 4099        bf16     42        26.9
+//   20000 x 4099        f32      61        49.9
+//   16384 x 8191        bf16     63        41.4
+//   32 x 1048576        f32      435       27 (workspace)
+lift_status gemv_by_rows(int64_t m, int64_t n, float alpha, int at, const void *A, int64_t lda, const float *x,
+                         float beta, float *y, int acc, char *ws, hipStream_t stream)
+{
+    const int eb = elem_bytes(at);
+    const int64_t e = 16 / eb;
+    int cus = 0;
+    lift_status st = cu_count(&cus);
+    if (st != LIFT_OK)
+        return st;
+    GemvRowsArgs a;
+    a.A = A;
+    a.x = x;
+    a.y = y;
+    a.m = m;
+    a.n = n;
+    a.lda = lda;
+    a.alpha = alpha;
+    a.beta = beta;
+    // 16-bit rows that start between two dwords have a head column; with an
+    // odd pitch every other row does
+    const bool odd_pitch = eb == 2 && lda % 2 != 0 && m > 1;
+    a.classes = odd_pitch ? 2 : 1;
+    a.heads = eb == 2 && (odd_pitch || !aligned(A, 4));
+    const int64_t P = a.classes;
+
+    const int64_t vecs = (n + e - 1) / e;      // 16-byte vectors of a row
+    if (vecs <= 64 * 8) {
+        // One wavefront step covers a row: as few lanes as do, several rows
+        // per wavefront.  8 / v rows in flight keep 8 loads per lane in
+        // flight; with fewer than 4 wavefronts per CU that way, one row each
+        // spreads the rows wider (1024 x 1024 fp32: 3.95 against 4.53 us).
+        // Fewer elements than one vector: element loads.
+        const int vb = n < e ? eb : 16;
+        int lanes = 8, v = 1, r = 8;
+        if (vb == 16) {
+            while (lanes < 64 && lanes < vecs)
+                lanes *= 2;
+            v = (int)((vecs + lanes - 1) / lanes);
+            r = 8 / v;
+        }
+        const int64_t side = lanes < 64 ? 64 / lanes : 1;
+        int64_t units = (m + side * r - 1) / (side * r);
+        if (vb == 16 && units < (int64_t)cus * 4) {
+            r = 1;
+            units = (m + side - 1) / side;
+        }
+        const void *kern = gemv_rows_table(at, acc, vb, lanes, v, r);
+        if (!kern)
+            return LIFT_EUNSUPPORTED;
+        // 8 work-groups per CU; 2 where a lane has more than one vector per
+        // row and so 6 to 8 loads in flight by itself (4096 x 4096 bf16: 8.1
+        // against 9.4, 16384 x 1000 bf16: 7.5 against 7.7, but 1000000 x 33
+        // fp32: 22.2 against 21.6 us)
+        const int64_t grid = std::min<int64_t>((units + 3) / 4, (int64_t)cus * (v > 1 ? 2 : 8));
+        return launch(kern, grid, 256, &a, stream);
+    }
+    if (vecs <= 64 * 8 * 8) {
+        // One work-group step covers a row: 3 .. 8 wavefronts x v vectors per
+        // lane with the least left over (ties: the fewest wavefronts).  The
+        // grid keeps about 40 KiB of loads in flight per CU (16 KiB rows:
+        // 2 work-groups per CU 49.9, 4: 53.7, 8: 54.0 us for 20000 x 4099
+        // fp32); rows of 32 KiB and more do better as more, shorter-lived
+        // work-groups (16384 x 8191 fp32: 16 per CU 80.3, 2 per CU 82.8 us)
+        // of at least 4 rows, each reading its part of x once (3000 x 25137
+        // bf16: one row each 35.6, 2 work-groups per CU 27.9 us).
+        int waves = 8, v = 8;
+        const int64_t need = (vecs + 63) / 64;
+        for (int w = 8; w >= 3; --w)
+            for (int q = 3; q <= 8; ++q)
+                if ((int64_t)w * q >= need && (int64_t)w * (q - 1) * 64 < vecs && w * q <= waves * v) {
+                    waves = w;
+                    v = q;
+                }
+        const void *kern = gemv_rows_wg_table(at, acc, v);
+        if (!kern)
+            return LIFT_EUNSUPPORTED;
+        const int64_t bytes = (int64_t)waves * v * 1024;
+        const int64_t per_cu = std::max<int64_t>(2, bytes >= 32768 ? std::min<int64_t>(16, m / (4 * (int64_t)cus)) : 40960 / bytes);
+        int64_t grid = std::min<int64_t>(m, (int64_t)cus * per_cu);
+        if (P == 2)
+            grid -= grid % 2;
+        return launch(kern, grid, waves * 64, &a, stream);
+    }
+    // Rows longer than that: panels of r rows, whole rows while there are
+    // enough of them (3000 x 25137 fp32: r = 4 49.1, 2: 50.9, 1: 56.8 us),
+    // else cut in chunks (at least 32 KiB each) so that one or two
+    // work-groups per CU come out as nearly even as can be.
+    const int64_t per_class = (m + P - 1) / P;
+    const int r = per_class * P >= (int64_t)cus * 8 ? 4 : per_class > 1 && (ws || per_class * P > cus) ? 2 : 1;
+    GemvPanelArgs p;
+    p.rows = a;
+    p.groups = P * ((per_class + r - 1) / r);
+    p.chunks = 1;
+    if (ws && p.groups <= cus) {
+        int64_t one = cus / p.groups, two = 2 * cus / p.groups;
+        int64_t c = two * p.groups * 100 > 2 * one * p.groups * 110 ? two : one;
+        c = std::min<int64_t>(c, std::max<int64_t>(1, n * eb / 32768));
+        c = std::min<int64_t>(c, MAX_WORKGROUPS / (p.groups * r));
+        p.chunks = std::max<int64_t>(1, c);
+    }
+    const int64_t nv = n / e;   // the head moves a boundary by one vector at most: the last chunk ends at the row
+    p.chunk = (nv + p.chunks - 1) / p.chunks;
+    p.chunks = std::max<int64_t>(1, (nv + p.chunk - 1) / p.chunk);
+    p.ws = ws;
+    const void *kern = gemv_panel_table(at, acc, r);
+    if (!kern)
+        return LIFT_EUNSUPPORTED;
+    return launch(kern, p.groups * p.chunks, 512, &p, stream);
+}
+
+bool all_zero(const lift_knobs *k)
+{
+    return !k->block && !k->vec_bytes && !k->unroll && !k->rows_per_wave && !k->split && !k->wg_per_cu &&
+           !k->row_split && !k->lanes_per_item && !k->interleave && !k->lane_form;
+}
+
+// ws (with ws_bytes): null, or the workspace of lift_gemv_ex_ws.
 lift_status gemv_common(int64_t m, int64_t n, float alpha, int at, const void *A, int64_t lda,
                         const float *x, float beta, float *y, int acc, const lift_knobs *knobs,
-                        hipStream_t stream)
+                        hipStream_t stream, void *ws = nullptr)
 {
     if (m < 0 || n < 0 || lda < std::max<int64_t>(1, n))
         return LIFT_EINVAL;
@@ -603,6 +766,7 @@ lift_status gemv_common(int64_t m, int64_t n, float alpha, int at, const void *A
     if (overlaps(y, m * 4, A, abytes) || overlaps(y, m * 4, x, m > 0 ? n * 4 : 0))
         return LIFT_EINVAL;
     lift_status st = LIFT_OK;
+    const lift_knobs *given = knobs;
     knobs = effective_knobs(knobs, TOP_GEMV, at, acc, m * n, &st, n);
     if (st != LIFT_OK)
         return st;
@@ -617,7 +781,13 @@ lift_status gemv_common(int64_t m, int64_t n, float alpha, int at, const void *A
     int vb = k.vec_bytes;
     int64_t e = vb / eb;
     const int64_t xalign = std::min<int64_t>(e * 4, 16);
-    if (n == 0 || !aligned(A, vb) || (lda * eb) % vb != 0 || !aligned(x, xalign)) {
+    const bool vec = n > 0 && aligned(A, vb) && (lda * eb) % vb == 0 && aligned(x, xalign);
+    // The launch is the library's choice: without knobs, unless a tuned entry
+    // (found on aligned rows) or the environment override decides it.
+    const bool choose = given ? all_zero(given) : !forced_config().present && (!knobs || !vec);
+    if (choose && n > 0)
+        return gemv_by_rows(m, n, alpha, at, A, lda, x, beta, y, acc, static_cast<char *>(ws), stream);
+    if (!vec) {
         vb = eb;
         e = 1;
     }
@@ -1330,6 +1500,19 @@ lift_status lift_gemv_ex(int64_t m, int64_t n, float alpha, lift_dtype at, const
                          const lift_knobs *knobs, hipStream_t stream)
 {
     return gemv_common(m, n, alpha, at, A, lda, x, beta, y, acc, knobs, stream);
+}
+
+lift_status lift_gemv_ex_ws(int64_t m, int64_t n, float alpha, lift_dtype at, const void *A, int64_t lda,
+                            const float *x, float beta, float *y, lift_acc acc, void *ws, size_t ws_bytes,
+                            const lift_knobs *knobs, hipStream_t stream)
+{
+    if (!ws || ws_bytes < lift_workspace_bytes())
+        return LIFT_EWORKSPACE;
+    if (!aligned(ws, 16))
+        return LIFT_EINVAL;
+    if (m > 0 && overlaps(y, m * 4, ws, (int64_t)ws_bytes))
+        return LIFT_EINVAL;
+    return gemv_common(m, n, alpha, at, A, lda, x, beta, y, acc, knobs, stream, ws);
 }
 
 lift_status lift_batch_create(const lift_problem *probs, int32_t count, lift_dtype storage, lift_acc acc,

@@ -92,6 +92,33 @@ struct GemvArgs {
     float beta;
 };
 
+// gemv over rows of any alignment (lift_gemv_rows.hpp).  `classes`: 2 where
+// 16-bit rows alternately start on and between dwords (an odd pitch), else 1;
+// `heads`: some row starts between two dwords.
+struct GemvRowsArgs {
+    const void *A;
+    const float *x;
+    float *y;
+    int64_t m;
+    int64_t n;
+    int64_t lda;
+    float alpha;
+    float beta;
+    int32_t classes;
+    int32_t heads;
+};
+
+// ... with the rows in `groups` groups of R and the columns in `chunks`
+// chunks of `chunk` vectors; ws: group counters and slots of the reduction
+// workspace (unused with one chunk).
+struct GemvPanelArgs {
+    GemvRowsArgs rows;
+    int64_t groups;
+    int64_t chunks;
+    int64_t chunk;
+    char *ws;
+};
+
 // ---- batched form ----------------------------------------------------------
 
 enum Kind { KIND_ASUM = 0, KIND_DOT = 1, KIND_GEMV = 2 };
@@ -182,5 +209,14 @@ const void *gemv_kernel_f16(int acc, int vec_bytes, int rows, int unroll);
 const void *gemv_split_kernel_f32(int acc, int vec_bytes, int rows, int unroll, bool x_stationary);
 const void *gemv_split_kernel_bf16(int acc, int vec_bytes, int rows, int unroll, bool x_stationary);
 const void *gemv_split_kernel_f16(int acc, int vec_bytes, int rows, int unroll, bool x_stationary);
+const void *gemv_rows_kernel_f32(int acc, int vec_bytes, int lanes, int v, int r);
+const void *gemv_rows_kernel_bf16(int acc, int vec_bytes, int lanes, int v, int r);
+const void *gemv_rows_kernel_f16(int acc, int vec_bytes, int lanes, int v, int r);
+const void *gemv_rows_wg_kernel_f32(int acc, int v);
+const void *gemv_rows_wg_kernel_bf16(int acc, int v);
+const void *gemv_rows_wg_kernel_f16(int acc, int v);
+const void *gemv_panel_kernel_f32(int acc, int r);
+const void *gemv_panel_kernel_bf16(int acc, int r);
+const void *gemv_panel_kernel_f16(int acc, int r);
 
 }  // namespace lift

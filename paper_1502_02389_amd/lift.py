@@ -100,6 +100,7 @@ SIGNATURES = {
     "lift_asum_ex": (_i32, [_i64, _i32, _vp, _i32, _i32, _vp, _vp, _sz, _kp, _vp]),
     "lift_dot_ex": (_i32, [_i64, _i32, _vp, _vp, _i32, _i32, _vp, _vp, _sz, _kp, _vp]),
     "lift_gemv_ex": (_i32, [_i64, _i64, _f32, _i32, _vp, _i64, _vp, _f32, _vp, _i32, _kp, _vp]),
+    "lift_gemv_ex_ws": (_i32, [_i64, _i64, _f32, _i32, _vp, _i64, _vp, _f32, _vp, _i32, _vp, _sz, _kp, _vp]),
     "lift_blackscholes": (_i32, [_i64, _vp, _f32, _f32, _f32, _f32, _vp, _vp]),
     "lift_blackscholes_ex": (_i32, [_i64, _vp, _f32, _f32, _f32, _f32, _vp, _kp, _vp]),
     "lift_md": (_i32, [_i64, _vp, _i64, _vp, _f32, _f32, _f32, _vp, _vp]),
@@ -195,6 +196,10 @@ def lift_dot_ex_noalloc(n, xt, x, y, acc, rt, result, knobs=None, stream=0):
 
 def lift_gemv_ex(m, n, alpha, at, A, lda, x, beta, y, acc, knobs=None, stream=0):
     return _lib().lift_gemv_ex(m, n, alpha, at, A, lda, x, beta, y, acc, _kptr(knobs), stream)
+
+
+def lift_gemv_ex_ws(m, n, alpha, at, A, lda, x, beta, y, acc, ws, ws_bytes, knobs=None, stream=0):
+    return _lib().lift_gemv_ex_ws(m, n, alpha, at, A, lda, x, beta, y, acc, ws, ws_bytes, _kptr(knobs), stream)
 
 
 def lift_blackscholes(n, s, strike, rate, volatility, years, call_put, stream=0):
@@ -487,8 +492,17 @@ def gemv(alpha, A, x, beta, y, acc="f32", knobs=None, lda=None):
         raise ValueError("y must have one entry per row of A")
     s = _stream_handle(A.device)
     accc = ACC[acc] if isinstance(acc, str) else int(acc)
-    _ok(lift_gemv_ex(m, n, float(alpha), _dtype_code(A.dtype), A.data_ptr(), lda, x.data_ptr(),
-                     float(beta), y.data_ptr(), accc, knobs, s), "lift_gemv")
+    if n * A.element_size() > 65536 and m <= 512 and not torch.cuda.is_current_stream_capturing():
+        # few long rows: split over work-groups through the stream's
+        # workspace.  Not under capture: a graph may be replayed on another
+        # stream, next to work that uses the same workspace.
+        ws = workspace(A.device)
+        st = lift_gemv_ex_ws(m, n, float(alpha), _dtype_code(A.dtype), A.data_ptr(), lda, x.data_ptr(),
+                             float(beta), y.data_ptr(), accc, ws.data_ptr(), ws.numel(), knobs, s)
+    else:
+        st = lift_gemv_ex(m, n, float(alpha), _dtype_code(A.dtype), A.data_ptr(), lda, x.data_ptr(),
+                          float(beta), y.data_ptr(), accc, knobs, s)
+    _ok(st, "lift_gemv")
     return y
 
 
