@@ -324,7 +324,10 @@ lift_status lift_blackscholes_ex(int64_t n, const float *s, float strike, float 
  * either way, the same way on every call.  epsilon finite, sigma > 0.
  * Binary32 throughout;
  * the sum over a list is split over the lanes given by lanes_per_item, in a
- * fixed order (deterministic).  LIFT_EINVAL for bad sizes, pointers or
+ * fixed order (deterministic).  Without knobs, systems of 2 to 4 times 5 MB of
+ * positions run as several launches (an armed timing hook spans them): the
+ * particles whose neighbours' indices are far from their own are summed a
+ * slice of positions at a time, `force` holding the sums so far.  LIFT_EINVAL for bad sizes, pointers or
  * parameters; n must be below 2^31, and n * lanes_per_item (one thread per
  * lane of each particle) below 2^32: with the default 16 lanes, n below
  * about 2^28. */

@@ -118,7 +118,7 @@ lift_status launch(const void *kernel, int64_t grid, int block, void *args, hipS
         return LIFT_EUNSUPPORTED;
     void *argv[] = {args};
     hipError_t e;
-    if (g_time_start) {
+    if (g_time_start || g_time_stop) {
         e = hipExtLaunchKernel(kernel, dim3((unsigned)grid), dim3((unsigned)block), argv, 0, s, g_time_start,
                                g_time_stop, 0);
         g_time_start = g_time_stop = nullptr;
@@ -1431,6 +1431,46 @@ lift_status lift_blackscholes(int64_t n, const float *s, float strike, float rat
     return lift_blackscholes_ex(n, s, strike, rate, volatility, years, call_put, nullptr, stream);
 }
 
+// MD in passes over slices of the positions (md_packed_kernel): the particles
+// whose neighbours lie near them are done by the first launch, the others
+// marked, and each pass adds their neighbours in one slice.  v: indices per
+// load of the first launch.
+static lift_status md_passes(const MdArgs &args, int slices, int v, hipStream_t stream)
+{
+    MdArgs a = args;
+    const int64_t span = (a.n + slices - 1) / slices;
+    a.near = (uint32_t)(span / 2);
+    const void *sort = md_sort_kernel_table(v), *packed = md_packed_kernel_table(std::min(v, 2));
+    if (!sort || !packed)
+        return LIFT_EUNSUPPORTED;
+    int cus = 0, fit = 1;
+    lift_status st = cu_count(&cus);
+    if (st == LIFT_OK)
+        st = resident_per_cu(packed, 256, &fit);
+    if (st != LIFT_OK)
+        return st;
+    // 4 work-groups per CU: the lists' and the gathers' lines compete for the
+    // L1's outstanding misses, more wavefronts only add to that (3 slices:
+    // 4 per CU 772, 6: 785, 8: 837 us)
+    const int64_t grid = std::min<int64_t>((a.n + 15) / 16, (int64_t)cus * std::min(fit, 4));
+    // an armed timing hook spans the launches
+    const hipEvent_t t0 = g_time_start, t1 = g_time_stop;
+    g_time_stop = nullptr;
+    st = launch(sort, (a.n * 8 + 255) / 256, 256, &a, stream);
+    for (int p = 0; p < slices && st == LIFT_OK; ++p) {
+        MdPackedArgs s;
+        s.md = a;
+        s.lo = (uint32_t)(p * span);
+        s.hi = (uint32_t)std::min<int64_t>(a.n, (p + 1) * span);
+        s.last = p == slices - 1;
+        if (s.last && t0)
+            g_time_stop = t1;
+        st = launch(packed, grid, 256, &s, stream);
+    }
+    g_time_start = g_time_stop = nullptr;
+    return st;
+}
+
 lift_status lift_md_ex(int64_t n, const float *pos, int64_t k, const int32_t *nbr, float cutoff,
                        float epsilon, float sigma, float *force, const lift_knobs *knobs,
                        hipStream_t stream)
@@ -1449,6 +1489,7 @@ lift_status lift_md_ex(int64_t n, const float *pos, int64_t k, const int32_t *nb
         !std::isfinite(epsilon))
         return LIFT_EINVAL;
     lift_status st = LIFT_OK;
+    const bool choose = !knobs && !forced_config().present;   // the launch is the library's choice
     knobs = effective_knobs(knobs, TOP_MD, LIFT_F32, LIFT_ACC_F32, n * k, &st);
     if (st != LIFT_OK)
         return st;
@@ -1456,9 +1497,22 @@ lift_status lift_md_ex(int64_t n, const float *pos, int64_t k, const int32_t *nb
     st = resolve(knobs, DEF_MD, 4, &kn);
     if (st != LIFT_OK)
         return st;
+    if (choose && !knobs) {
+        // 16 lanes per particle while 8 would leave wavefront slots empty
+        // (12288 particles, 128 slots: 5.9 against 6.6 us), else 8 (176400:
+        // 28 against 31 us in lattice order, 67 against 70 in random order),
+        // with as many loads in flight as cover a row and no more (a load past
+        // the row still costs its pairs' arithmetic: 38 us)
+        const int64_t kv = (k + 3) / 4;
+        kn.lanes = n < 65536 && kv >= 16 ? 16 : 8;
+        kn.unroll = 1;
+        while (kn.unroll < 4 && (int64_t)kn.lanes * kn.unroll < kv)
+            kn.unroll *= 2;
+    }
     if (kn.vec_bytes < 4 || kn.unroll > 4)
         return LIFT_EINVAL;
-    if (n * kn.lanes > MAX_DISPATCH_ITEMS - kn.block)  // one thread per lane of each particle
+    // one thread per lane of each particle (16 lanes where the library chooses)
+    if (n * (choose ? DEF_MD.lanes : kn.lanes) > MAX_DISPATCH_ITEMS - kn.block)
         return LIFT_EINVAL;
     if (n == 0)
         return LIFT_OK;
@@ -1478,6 +1532,14 @@ lift_status lift_md_ex(int64_t n, const float *pos, int64_t k, const int32_t *nb
     a.t2 = (float)((double)cutoff * (double)cutoff);
     a.sigma2 = (float)((double)sigma * (double)sigma);
     a.eps24 = (float)(24.0 * (double)epsilon);
+    a.near = 0;
+    // Slices of about 5 MB of positions (an XCD's L2 holds 4 MiB), where there
+    // are 2 to 4 of them: up to 6 MB one pass is faster (512000 particles in
+    // random order, 8.2 MB: 363 us, 2 slices 300 us), and beyond 4 the lists'
+    // extra readings cost what the misses did.
+    const int slices = (int)std::min<int64_t>(5, (n * 16 + 2500000) / 5000000);
+    if (choose && k > 0 && slices >= 2 && slices <= 4)
+        return md_passes(a, slices, v, stream);
     const int64_t threads = n * kn.lanes;
     const int64_t grid = (threads + kn.block - 1) / kn.block;
     return launch(kern, grid, kn.block, &a, stream);

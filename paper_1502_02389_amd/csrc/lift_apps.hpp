@@ -32,8 +32,20 @@ struct MdArgs {
     float t2;      // binary32(cutoff^2)
     float sigma2;  // sigma^2
     float eps24;   // 24 epsilon
+    uint32_t near; // SORT instances: an index within this of a particle's own is near it
 };
 
+// One pass of MD over the neighbours in [lo, hi), for the particles whose
+// force is marked; k >= 1, a multiple of the instance's V.
+struct MdPackedArgs {
+    MdArgs md;
+    uint32_t lo;
+    uint32_t hi;
+    int32_t last;   // the last pass: clears the marks
+};
+
+const void *md_sort_kernel_table(int v);
+const void *md_packed_kernel_table(int v);
 const void *blackscholes_kernel_table(int vec_bytes, int unroll);
 const void *md_kernel_table(int lanes, int v, int unroll);
 

@@ -63,7 +63,27 @@ __device__ __forceinline__ float group_sum(float v)
     return v;
 }
 
-template <int L, int V, int U>
+// One neighbour's term, added to the particle's force where `use`.
+__device__ __forceinline__ void add_pair(const MdArgs &a, const f32x4 &p, const f32x4 &q, bool use, float &fx, float &fy,
+                                         float &fz)
+{
+    const float dx = p[0] - q[0], dy = p[1] - q[1], dz = p[2] - q[2];
+    const float r2 = (dx * dx + dy * dy) + dz * dz;
+    const float r2inv = __builtin_amdgcn_rcpf(r2);
+    const float s2 = a.sigma2 * r2inv;
+    const float s6 = s2 * s2 * s2;
+    const float fs = a.eps24 * r2inv * s6 * fmaf(2.f, s6, -1.f);  // 2 s6 is exact: one rounding either way
+    const float fh = use && r2 < a.t2 ? fs : 0.f;
+    fx = fmaf(fh, dx, fx);
+    fy = fmaf(fh, dy, fy);
+    fz = fmaf(fh, dz, fz);
+}
+
+// SORT: the first of several launches (see md_packed_kernel).  A wavefront
+// whose first particle lists a neighbour (among its first 32) that is more
+// than half a slice of positions away leaves its particles to the passes,
+// marked by a 1 in the fourth component of their forces.
+template <int L, int V, int U, bool SORT = false>
 __global__ void __launch_bounds__(1024) md_kernel(MdArgs a)
 {
     using IV = typename IdxVec<V>::type;
@@ -72,6 +92,16 @@ __global__ void __launch_bounds__(1024) md_kernel(MdArgs a)
     const int sub = (int)(gt % L);
     if (i >= a.n)  // whole groups leave together (L divides 64)
         return;
+    if constexpr (SORT) {
+        const int lane = threadIdx.x & 63;
+        const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)i), half = a.near;
+        const uint32_t id = lane < 32 && lane < a.k ? (uint32_t)a.nbr[first * a.k + lane] : ~0u;
+        if (__ballot(id < (uint32_t)a.n && id - (first - half) > 2 * half)) {
+            if (sub == 0)
+                reinterpret_cast<f32x4 *>(a.force)[i] = f32x4{0.f, 0.f, 0.f, 1.f};
+            return;
+        }
+    }
     const f32x4 *pos = reinterpret_cast<const f32x4 *>(a.pos);
     const f32x4 p = pos[i];
     const IV *row = reinterpret_cast<const IV *>(a.nbr + i * a.k);
@@ -103,18 +133,8 @@ __global__ void __launch_bounds__(1024) md_kernel(MdArgs a)
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int e = 0; e < V; ++e) {
-                const float dx = p[0] - q[u][e][0], dy = p[1] - q[u][e][1], dz = p[2] - q[u][e][2];
-                const float r2 = (dx * dx + dy * dy) + dz * dz;
-                const float r2inv = __builtin_amdgcn_rcpf(r2);
-                const float s2 = a.sigma2 * r2inv;
-                const float s6 = s2 * s2 * s2;
-                const float fs = a.eps24 * r2inv * s6 * (2.f * s6 - 1.f);
-                const float fh = use[u][e] && r2 < a.t2 ? fs : 0.f;
-                fx = fmaf(fh, dx, fx);
-                fy = fmaf(fh, dy, fy);
-                fz = fmaf(fh, dz, fz);
-            }
+            for (int e = 0; e < V; ++e)
+                add_pair(a, p, q[u][e], use[u][e], fx, fy, fz);
     }
     fx = group_sum<L>(fx);
     fy = group_sum<L>(fy);
@@ -122,6 +142,163 @@ __global__ void __launch_bounds__(1024) md_kernel(MdArgs a)
     if (sub == 0) {
         f32x4 f = {fx, fy, fz, 0.f};
         reinterpret_cast<f32x4 *>(a.force)[i] = f;
+    }
+}
+
+// MD in passes, for positions that do not fit one XCD's L2 and particles in
+// no spatial order.  There the single-pass kernel waits for gathers that miss:
+// a position is 16 bytes, the line it comes in 128 (2^20 particles in random
+// order: 65.7 M misses, 8.4 GB for 0.57 GB of lists, positions and forces,
+// 1090 us).  Each pass wants only the neighbours in one slice of the
+// positions, which then stays in the L2, and adds to the force; reading the
+// lists again costs about 107 us per pass there, so three slices of 5.6 MB do
+// best (2: 880, 3: 765, 4: 840, 6: 1050 us).
+//
+// A wavefront takes blocks of four marked particles (md_kernel's SORT form).
+// It first packs the wanted neighbours of each list in LDS -- 64 lanes over
+// the list, an index's place being the count of wanted ones before it, from a
+// ballot -- and then 16 lanes per particle work through the packed list, so
+// that the slots another pass wants cost a few instructions each instead of a
+// pair's arithmetic.  It reads the marks of 64 of its blocks at once: with
+// none marked a pass costs one round trip.  The last pass clears the marks.
+template <int V>
+__global__ void __launch_bounds__(256) md_packed_kernel(MdPackedArgs s)
+{
+    constexpr int L = 16, U = 2 / V, STEP = 128;   // indices per particle and step: 64 lanes x U x V
+    constexpr int PITCH = STEP + 16;               // the four particles of a wave in different banks
+    using IV = typename IdxVec<V>::type;
+    __shared__ int32_t lds[4][4][PITCH];
+    const MdArgs &a = s.md;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, sub = lane % L, grp = lane / L;
+    int32_t(*list)[PITCH] = lds[wv];
+    const int64_t wave = (int64_t)blockIdx.x * 4 + wv, nwaves = (int64_t)gridDim.x * 4;
+    const int64_t nblocks = (a.n + 3) / 4;
+    const f32x4 *pos = reinterpret_cast<const f32x4 *>(a.pos);
+    f32x4 *force = reinterpret_cast<f32x4 *>(a.force);
+    const int kv = (int)(a.k / V);
+
+    int64_t base = 0;          // `mask`: which of this wave's blocks base .. base + 63 are to be done
+    uint64_t mask = 0;
+    const auto fill = [&] {
+        const int64_t b = wave + (base + lane) * nwaves;
+        mask = __ballot(b < nblocks && force[min(b, nblocks - 1) * 4][3] != 0.f);
+    };
+    const auto next_block = [&]() -> int64_t {   // wave-uniform; -1: none left
+        while (mask == 0) {
+            base += 64;
+            if (wave + base * nwaves >= nblocks)
+                return -1;
+            fill();
+        }
+        const int j = __builtin_ctzll(mask);
+        mask &= mask - 1;
+        return wave + (base + j) * nwaves;
+    };
+
+    IV iv[4][U];
+    f32x4 p;
+    const auto load = [&](int64_t blk, int step0) {   // the four particles' indices and positions
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const IV *row = reinterpret_cast<const IV *>(a.nbr + min(blk * 4 + g, a.n - 1) * a.k);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                iv[g][u] = __builtin_nontemporal_load(row + min(step0 + lane + 64 * u, kv - 1));
+        }
+        p = pos[min(blk * 4 + grp, a.n - 1)];
+    };
+
+    fill();
+    int64_t blk = next_block();
+    if (blk < 0)
+        return;
+    int step0 = 0;
+    float fx = 0.f, fy = 0.f, fz = 0.f;
+    load(blk, 0);
+    while (true) {
+        const f32x4 mine = p;
+        const int64_t i = blk * 4 + grp;
+        const uint32_t lo = s.lo, width = s.hi - s.lo;
+        int count[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            count[g] = 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                    const int32_t id = lane_of<V>(iv[g][u], e);
+                    const bool want = step0 + lane + 64 * u < kv && (uint32_t)id - lo < width;
+                    const uint64_t who = __ballot(want);
+                    if (want)
+                        list[g][__builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32),
+                                                          __builtin_amdgcn_mbcnt_lo((uint32_t)who, count[g]))] = id;
+                    count[g] += __popcll(who);
+                }
+        }
+        __builtin_amdgcn_wave_barrier();   // one wave writes and reads `list`: LDS keeps its order
+        const int most = max(max(count[0], count[1]), max(count[2], count[3]));
+        const int have = grp & 2 ? (grp & 1 ? count[3] : count[2]) : (grp & 1 ? count[1] : count[0]);
+        const int32_t *from = list[grp] + sub;
+        const bool row_done = step0 + 64 * U >= kv;
+        int64_t nblk = blk;
+        int nstep = step0 + 64 * U;
+        f32x4 prev = {0.f, 0.f, 0.f, 0.f};
+        for (int r = 0; r < most || r == 0; r += 2 * L) {
+            const bool v0 = r + sub < have, v1 = r + L + sub < have;
+            f32x4 q0 = mine, q1 = mine;
+            if (v0)
+                q0 = pos[from[r]];
+            if (v1)
+                q1 = pos[from[r + L]];
+            if (r == 0) {
+                // the next step's indices, behind the first gathers
+                if (row_done) {
+                    if (sub == 0 && i < a.n)
+                        prev = force[i];
+                    nblk = next_block();
+                    nstep = 0;
+                }
+                if (nblk >= 0)
+                    load(nblk, nstep);
+            }
+            loads_in_flight();
+            add_pair(a, mine, q0, v0, fx, fy, fz);
+            add_pair(a, mine, q1, v1, fx, fy, fz);
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (row_done) {
+            fx = group_sum<L>(fx);
+            fy = group_sum<L>(fy);
+            fz = group_sum<L>(fz);
+            if (sub == 0 && i < a.n)
+                force[i] = f32x4{prev[0] + fx, prev[1] + fy, prev[2] + fz, s.last ? 0.f : 1.f};
+            fx = fy = fz = 0.f;
+            if (nblk < 0)
+                return;
+        }
+        blk = nblk;
+        step0 = nstep;
+    }
+}
+
+const void *md_sort_kernel_table(int v)
+{
+    switch (v) {
+    case 1: return reinterpret_cast<const void *>(&md_kernel<8, 1, 4, true>);
+    case 2: return reinterpret_cast<const void *>(&md_kernel<8, 2, 4, true>);
+    case 4: return reinterpret_cast<const void *>(&md_kernel<8, 4, 4, true>);
+    default: return nullptr;
+    }
+}
+
+const void *md_packed_kernel_table(int v)
+{
+    switch (v) {
+    case 1: return reinterpret_cast<const void *>(&md_packed_kernel<1>);
+    case 2: return reinterpret_cast<const void *>(&md_packed_kernel<2>);
+    default: return nullptr;
     }
 }
 

@@ -224,3 +224,87 @@ def test_large_system(gpu_device, launch, shuffle):
     banner("md 2^20 particles", launch, "random order" if shuffle else "lattice order")
     f = _md_plain(pos, nbr, params, defaults=launch == "library defaults")
     check(f, pos, nbr, params)
+
+
+# ------------------------------------------------------------------ passes over slices of the positions
+
+
+def _large_system(n, k, order, seed, device):
+    """n particles on a jittered line of unit cells (1024 x 32 lattice planes),
+    every particle's k neighbours among the nearest lattice offsets; the
+    particle order is the lattice's, random, or random in its first half.
+    Built on the GPU (the oracle sees the same bits)."""
+    g = torch.Generator(device)
+    g.manual_seed(seed)
+    i = torch.arange(n, device=device)
+    ny, nz = 32, 32
+    c = torch.stack([i // (ny * nz), i // nz % ny, i % nz], 1)
+    pos = torch.zeros((n, 4), device=device)
+    where = c.to(torch.float32) + torch.rand((n, 3), generator=g, device=device) * 0.2 - 0.1
+    perm = i.clone()
+    if order == "random":
+        perm = torch.randperm(n, generator=g, device=device)
+    elif order == "mixed":
+        perm[: n // 2] = torch.randperm(n // 2, generator=g, device=device)
+    old = torch.empty_like(perm)
+    old[perm] = i
+    pos[:, :3] = where[old]
+    co = c[old]
+    offs = sorted((a * a + b * b + d * d, a, b, d) for a in range(-2, 3) for b in range(-2, 3) for d in range(-2, 3)
+                  if (a, b, d) != (0, 0, 0))
+    nbr = torch.full((n, k), -1, dtype=torch.int32, device=device)
+    nx = (n + ny * nz - 1) // (ny * nz)
+    for j, (_, a, b, d) in enumerate(offs[:k]):
+        x, y, z = co[:, 0] + a, co[:, 1] + b, co[:, 2] + d
+        at = (x * ny + y) * nz + z
+        ok = (x >= 0) & (x < nx) & (y >= 0) & (y < ny) & (z >= 0) & (z < nz) & (at < n)
+        nbr[:, j] = torch.where(ok, perm[torch.where(ok, at, 0)], -1).to(torch.int32)
+    return pos.contiguous(), nbr
+
+
+@pytest.mark.parametrize("n,k,order", [(468_753, 24, "random"), (500_001, 20, "mixed"), (700_002, 13, "random"),
+                                       (1_100_007, 6, "random"), (600_000, 18, "lattice"), (480_000, 124, "random")])
+def test_passes_over_slices(gpu_device, n, k, order):
+    """Systems of 2, 3 and 4 slices (and a row length of each index width, rows
+    longer than 64 and padding within them): forces as the oracle has them,
+    fourth component 0, whatever the output held before, on every run the same bits."""
+    pos, nbr = _large_system(n, k, order, n % 1000, DEV)
+    params = (W.MD_CUTOFF, W.MD_EPSILON, W.MD_SIGMA)
+    banner("md passes", n, k, order)
+    out = torch.full((n, 4), float("nan"), device=DEV)
+    L.md(pos, nbr, *params, out=out)
+    first = out.clone()
+    out.fill_(1.0)
+    L.md(pos, nbr, *params, out=out)
+    assert torch.equal(first.view(torch.int32), out.view(torch.int32))
+    check(out, pos.cpu(), nbr.cpu(), params)
+
+
+def test_passes_in_a_graph_and_under_the_timing_hook(gpu_device):
+    n, k = 520_000, 10
+    pos, nbr = _large_system(n, k, "random", 5, DEV)
+    params = (W.MD_CUTOFF, W.MD_EPSILON, W.MD_SIGMA)
+    want = L.md(pos, nbr, *params)
+    ev = L.HipEvents(2)
+    banner("md passes timed")
+    try:
+        assert L.lift_time_next_launch(ev.events[0], ev.events[1]) == 0
+        got = L.md(pos, nbr, *params)
+        torch.cuda.synchronize()
+        assert 0.0 < ev.elapsed_ms(0, 1) < 50.0
+        assert torch.equal(got, want)
+    finally:
+        ev.close()
+    s = torch.cuda.Stream(device=DEV)
+    out = torch.empty((n, 4), device=DEV)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(s):
+        s.wait_stream(torch.cuda.default_stream())
+        with torch.cuda.graph(graph, stream=s):
+            L.md(pos, nbr, *params, out=out)
+        for _ in range(3):
+            out.fill_(float("nan"))
+            graph.replay()
+            s.synchronize()
+            assert torch.equal(out, want)
+    graph.reset()
