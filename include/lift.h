@@ -34,9 +34,8 @@
  *             paper's reduce returns a one-element array, T[] -> T[1].
  * Workspace.  asum and dot take a device workspace `ws` of `ws_bytes` bytes,
  *             at least lift_workspace_bytes().  It must be zero-filled ONCE
- *             before its first use; every call leaves it zeroed again (the
- *             last work-group resets the counter it uses), so replays need
- *             no memset.  Calls that may run concurrently (different streams)
+ *             before its first use; every call leaves the counters and arrival
+ *             marks it uses zeroed again, so replays need no memset.  Calls that may run concurrently (different streams)
  *             need different workspaces.
  * Errors.     Arguments are checked before any HIP call.  LIFT_EINVAL: bad
  *             size, null pointer with a non-empty extent, pointer not aligned
@@ -56,12 +55,11 @@
  *             results under every knob set.  The cross-work-group combine
  *             relies on gfx950's memory behaviour rather than on fences:
  *             partials are written with agent-scope atomic stores (which the
- *             hardware writes through past the XCD-private L2), a work-group
- *             counts in on the arrival counters only after its store has
- *             completed (a wait on the store, not a release fence, which
- *             would write back the whole L2), and the combining work-group
- *             reads the partials with agent-scope atomic loads (which miss
- *             the L2).  Built and tested for gfx950 only.
+ *             hardware writes through past the XCD-private L2) of one word
+ *             that shows its arrival by itself, and the combining work-group,
+ *             the last of the grid, reads them with agent-scope atomic loads
+ *             (which miss the L2) until all are there.  Built and tested for
+ *             gfx950 only.
  */
 #ifndef LIFT_H
 #define LIFT_H

@@ -488,12 +488,9 @@ __global__ void __launch_bounds__(512) gemv_panel_kernel(GemvPanelArgs a)
             a.rows.y[r0 + t * P] = row_epilogue<ACC>(d, a.rows.alpha, a.rows.beta, yold);
         return;
     }
-    char *slots = a.ws + WS_HEADER + group * a.chunks * R * WS_SLOT;   // [row][chunk]
+    const int64_t slot0 = group * a.chunks * R;   // [row][chunk]
     if (t < R)
-        store_coherent(slots + ((int64_t)t * a.chunks + chunk) * WS_SLOT, d);
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_s_waitcnt(0);  // the partials' stores have completed
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        store_word(slot_word(a.ws, slot0 + t * a.chunks + chunk), to_word(d));
     unsigned *counter = reinterpret_cast<unsigned *>(a.ws + WS_GROUPS + group * WS_GROUP_STRIDE);
     int last = 0;
     if (t == 0)
@@ -505,8 +502,17 @@ __global__ void __launch_bounds__(512) gemv_panel_kernel(GemvPanelArgs a)
 #pragma unroll
     for (int i = 0; i < R; ++i) {
         D s = zero_of<D>();
-        for (int64_t c = t; c < a.chunks; c += 64)
-            s = merge(s, load_coherent<D>(slots + ((int64_t)i * a.chunks + c) * WS_SLOT));
+        for (int64_t c = t; c < a.chunks; c += 64) {
+            // every chunk's store was issued before its arrival was counted:
+            // at most its way to memory is left to wait for
+            uint64_t *slot = slot_word(a.ws, slot0 + i * a.chunks + c);
+            uint64_t w;
+            do {
+                w = load_word(slot);
+            } while (!word_arrived<D>(w));
+            store_word(slot, 0);
+            s = merge(s, from_word<D>(w));
+        }
         s = lanes_sum<64>(s);
         if (t == i)
             sum = s;

@@ -12,20 +12,18 @@
 //
 // term(a) = |a| (asum) or a_x * a_y (dot, zip fused into the load).  The
 // final reduce-seq o join runs in the same launch: every work-group stores
-// its partial, then counts in on agent-scope arrival counters (two levels,
-// see arrive()); in the one that arrives last, one wavefront folds all
-// partials (lane t: partials t, t + 64, ...; then the wave butterfly) and
-// writes the result, then resets the counter for the next call.  No float
-// atomics
-// and no inter-work-group waiting, so the result is deterministic and the
-// grid always drains.
+// its partial with a tag that shows its arrival, and one wavefront of the
+// grid's last work-group folds all partials (lane t: partials t, t + 64, ...;
+// then the wave butterfly) as they arrive, writes the result and clears the
+// tags for the next call.  No float atomics, so the result is deterministic;
+// only the work-group dispatched last ever waits, and only for work-groups
+// that do not, so the grid always drains.
 //
 // Cross-XCD visibility without cache maintenance: the partials are written
 // and read with agent-scope atomic stores / loads, which gfx950 performs
-// device-coherently (write-through / miss in the per-XCD L2), and a
-// work-group counts in only once its partial's store has completed.  An agent-scope
-// release/acquire fence would instead write back and invalidate the whole
-// L2 of the XCD in every work-group.
+// device-coherently (write-through / miss in the per-XCD L2), value and tag in
+// one word.  An agent-scope release/acquire fence would instead write back and
+// invalidate the whole L2 of the XCD in every work-group.
 #pragma once
 
 #include "lift_device.hpp"
@@ -200,6 +198,63 @@ __device__ __forceinline__ Pair load_coherent<Pair>(const char *p)
                                                       __HIP_MEMORY_SCOPE_AGENT));
 }
 
+// Partials whose arrival shows in the slot itself: one 64-bit word per
+// partial, written by one store, so a reader sees all of it or none and needs
+// no counter and no ordering between stores.  A word of zeros (the workspace
+// before its first use, and again once the reader has cleared what it took)
+// or of ones has not arrived:
+//   binary32       : the value and a tag;
+//   (sum, error)   : the pair XOR a constant whose sum half is a signalling
+//                    NaN; both halves come out of additions, which never
+//                    return one, so the word is not 0, and not ~0 as the
+//                    complement's error half is one too;
+//   binary64       : the value XOR a signalling NaN; ~0 would be a subnormal,
+//                    and these partials are sums of binary32 values and
+//                    products, multiples of 2^-298.
+constexpr uint32_t SLOT_TAG = 0x4c494654u;
+constexpr uint64_t SLOT_PAIR = 0x805ffffe7fa5c3e1ull;   // error half above, sum half below
+constexpr uint64_t SLOT_F64 = 0x7ff4c3e15a96f00dull;
+
+__device__ __forceinline__ uint64_t to_word(float v)
+{
+    return ((uint64_t)SLOT_TAG << 32) | __builtin_bit_cast(uint32_t, v);
+}
+__device__ __forceinline__ uint64_t to_word(double v) { return __builtin_bit_cast(uint64_t, v) ^ SLOT_F64; }
+__device__ __forceinline__ uint64_t to_word(Pair v) { return __builtin_bit_cast(uint64_t, v) ^ SLOT_PAIR; }
+template <class S>
+__device__ __forceinline__ bool word_arrived(uint64_t w)
+{
+    if constexpr (sizeof(S) == 4)
+        return (uint32_t)(w >> 32) == SLOT_TAG;
+    else
+        return w + 1 > 1;   // neither 0 nor ~0
+}
+template <class S>
+__device__ __forceinline__ S from_word(uint64_t w);
+template <> __device__ __forceinline__ float from_word<float>(uint64_t w) { return bits_to_float((uint32_t)w); }
+template <> __device__ __forceinline__ double from_word<double>(uint64_t w)
+{
+    return __builtin_bit_cast(double, w ^ SLOT_F64);
+}
+template <> __device__ __forceinline__ Pair from_word<Pair>(uint64_t w)
+{
+    return __builtin_bit_cast(Pair, w ^ SLOT_PAIR);
+}
+// The word of partial i is the second half of its 16-byte slot; the untagged
+// partials of other kernels (the small lane forms) go into the first.
+__device__ __forceinline__ uint64_t *slot_word(char *ws, int64_t i)
+{
+    return reinterpret_cast<uint64_t *>(ws + WS_HEADER + i * WS_SLOT + 8);
+}
+__device__ __forceinline__ void store_word(uint64_t *p, uint64_t w)
+{
+    __hip_atomic_store(p, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t load_word(const uint64_t *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Two-level arrival of this work-group (called by one thread, after its
 // partial's store has completed).  Work-group b counts in on the group
 // counter at group_base + (b / ARRIVAL_GROUP) * WS_GROUP_STRIDE; the last of
@@ -218,6 +273,16 @@ __device__ __forceinline__ bool arrive(unsigned *global, char *group_base)
     __hip_atomic_store(gc, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     prev = __hip_atomic_fetch_add(global, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return prev == groups - 1;
+}
+
+// Lane 0's value, for the whole wave.
+__device__ __forceinline__ float first_lane(float v) { return readlane(v, 0); }
+__device__ __forceinline__ Pair first_lane(Pair v) { return {readlane(v.s, 0), readlane(v.c, 0)}; }
+__device__ __forceinline__ double first_lane(double v)
+{
+    const uint64_t w = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)w), hi = __builtin_amdgcn_readfirstlane((uint32_t)(w >> 32));
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
 template <class S>
@@ -271,9 +336,9 @@ __device__ __forceinline__ void stamp(const ReduceArgs &a, int k)
     }
 }
 
-// Stamped instances, thread 0 of a work-group whose arrival is counted:
-// the arrival time (also its end, unless it combines), its ids and whether
-// it combines.  A single work-group stamps its partial's store here too.
+// Stamped instances, thread 0 of a work-group whose partial is on its way:
+// the time (store, arrival and end alike, unless it combines), its ids and
+// whether it combines.
 template <bool STAMP>
 __device__ __forceinline__ void stamp_arrival(const ReduceArgs &a, int last)
 {
@@ -281,8 +346,7 @@ __device__ __forceinline__ void stamp_arrival(const ReduceArgs &a, int last)
         __builtin_amdgcn_sched_barrier(0);
         uint64_t *w = a.stamps + (int64_t)blockIdx.x * STAMPS_PER_WG;
         const uint64_t now = (uint64_t)wall_clock64();
-        if (gridDim.x == 1)
-            w[3] = now;
+        w[3] = now;
         w[4] = now;
         w[5] = now;
         const uint32_t xcc = __builtin_amdgcn_s_getreg((20 << 0) | (0 << 6) | (3 << 11));  // XCC_ID[3:0]
@@ -291,13 +355,56 @@ __device__ __forceinline__ void stamp_arrival(const ReduceArgs &a, int last)
     }
 }
 
+// Lane t of a wavefront folds partials t, t + 64, ... of [0, last) and
+// `own`, partial `last`, into v in that order, each as soon as it is there,
+// and clears the slots.  LOADS loads in flight, all issued again while one of
+// them is missing.
+template <class ST, int LOADS>
+__device__ __forceinline__ void fold_slots(char *ws, int64_t last, ST own, ST &v)
+{
+    const int t = threadIdx.x & 63;
+    for (int64_t base = 0; base <= last; base += 64 * LOADS) {
+        uint64_t w[LOADS];
+        bool waits;
+        do {
+#pragma unroll
+            for (int k = 0; k < LOADS; ++k)
+                w[k] = load_word(slot_word(ws, min(base + t + 64 * k, last - 1)));
+            waits = false;
+#pragma unroll
+            for (int k = 0; k < LOADS; ++k)
+                waits |= base + t + 64 * k < last && !word_arrived<ST>(w[k]);
+        } while (__any(waits));
+#pragma unroll
+        for (int k = 0; k < LOADS; ++k) {
+            const int64_t i = base + t + 64 * k;
+            if (i < last)
+                store_word(slot_word(ws, i), 0);
+            if (i <= last)
+                v = merge(v, i == last ? own : from_word<ST>(w[k]));
+        }
+    }
+}
+
 // The work-group's partial wg (valid in thread 0; every thread calls this
 // after the work-group tree) goes to the combine: with one work-group it is
-// the result; else it is stored to its slot and counted in, and in the
-// work-group that arrives last one wavefront folds all partials -- lane t
-// folds partials t, t + 64, t + 128, ... in that order (COMBINE_LOADS loads
-// in flight), then the wave butterfly -- and writes the result.  No barrier
-// on this path.
+// the result; else every work-group but the last of the grid stores it, tagged,
+// and is done, and one wavefront of the last one folds all partials as they
+// arrive -- lane t folds partials t, t + 64, t + 128, ... in that order
+// then the wave butterfly -- and writes the
+// result.  No barrier on this path.
+//
+// The last work-group waits for the others, which wait for nothing: all of
+// them are dispatched before it, so they run or have run when it starts.
+// Against a wait for the store's completion, two levels of arrival counters
+// and the last arriver reading the slots (four dependent device-scope round
+// trips), this leaves the store's way and the read's.  Back to back in a HIP
+// graph, before and now (us): asum fp32 of 2^16 3.8 -> 2.9, 2^18 4.0 -> 3.2,
+// 2^20 4.6 -> 3.4, 2^24 14.0 -> 13.4; compensated bf16 of 2^22 5.9 -> 4.8.
+// The loads of a round are what the poll costs (each of the 64 lanes is its
+// own device-scope request), hence one word per partial and 4 loads per lane
+// where they do: with two words per partial the compensated form gained
+// nothing, and re-reading only what is missing lost what fp32 had gained.
 template <int ACC, bool STAMP>
 __device__ __forceinline__ void combine_partials(const ReduceArgs &a, typename BlockT<ACC>::type wg)
 {
@@ -315,44 +422,29 @@ __device__ __forceinline__ void combine_partials(const ReduceArgs &a, typename B
     // values (block_sum ends with a barrier).
     if (t >= 64)
         return;
-    char *slots = reinterpret_cast<char *>(a.ws) + WS_HEADER;  // 16-byte slots
-    int last = 0;
-    if (t == 0) {
-        store_coherent(slots + (int64_t)blockIdx.x * WS_SLOT, to_slot<ACC>(wg));
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        __builtin_amdgcn_s_waitcnt(0);  // the partial's store has completed
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        if constexpr (STAMP) {
-            __builtin_amdgcn_sched_barrier(0);
-            stamp<STAMP>(a, 3);
-            __builtin_amdgcn_sched_barrier(0);
+    char *ws = reinterpret_cast<char *>(a.ws);
+    const int64_t last = (int64_t)gridDim.x - 1;
+    ST own = to_slot<ACC>(wg);
+    if (blockIdx.x != last) {
+        if (t == 0) {
+            store_word(slot_word(ws, blockIdx.x), to_word(own));
+            stamp_arrival<STAMP>(a, 0);
         }
-        last = arrive(reinterpret_cast<unsigned *>(a.ws), reinterpret_cast<char *>(a.ws) + WS_GROUPS) ? 1 : 0;
-        stamp_arrival<STAMP>(a, last);  // after the arrival's atomics have returned (last depends on them)
-    }
-    last = __builtin_amdgcn_readfirstlane(last);  // lane 0's decision, for the whole wave
-    if (!last)
         return;
+    }
+    if (t == 0)
+        stamp_arrival<STAMP>(a, 1);
 
     // the final reduce-seq o join, by this wavefront
-    constexpr int COMBINE_LOADS = 8;
-    const int64_t G = gridDim.x;
+    own = first_lane(own);
     ST v = zero_of<ST>();
-    for (int64_t base = 0; base < G; base += 64 * COMBINE_LOADS) {
-        ST p[COMBINE_LOADS];
-#pragma unroll
-        for (int k = 0; k < COMBINE_LOADS; ++k)
-            p[k] = load_coherent<ST>(slots + min(base + t + 64 * k, G - 1) * WS_SLOT);
-#pragma unroll
-        for (int k = 0; k < COMBINE_LOADS; ++k)
-            if (base + t + 64 * k < G)
-                v = merge(v, p[k]);
-    }
+    if (last < 4 * 64)
+        fold_slots<ST, 4>(ws, last, own, v);
+    else
+        fold_slots<ST, 8>(ws, last, own, v);
     v = wave_sum(v);
-    if (t == 0) {
+    if (t == 0)
         write_result(a.result, a.result_f64, v);
-        __hip_atomic_store(reinterpret_cast<unsigned *>(a.ws), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
     if constexpr (STAMP) {
         __builtin_amdgcn_sched_barrier(0);
         stamp<STAMP>(a, 5);
