@@ -2,7 +2,7 @@
 
 ``python -m paper_1502_02389_amd.build`` compiles every translation unit under
 ``csrc/`` in parallel into ``_build/`` and links the shared library next to
-this file.  All device code is compiled with packed-FP32 instructions
+this file, and the binding's native route (``_tensor_calls.so``, g++) beside it.  All device code is compiled with packed-FP32 instructions
 disabled and without floating-point contraction (fma is written explicitly
 where the arithmetic wants it).
 
@@ -124,8 +124,32 @@ def sanitizer_env(oracle_lib: str | None = None) -> dict:
     return env
 
 
+# The binding's native route: host code only, against the installed torch.
+TENSOR_CALLS = os.path.join(HERE, "_tensor_calls.so")
+TENSOR_CALLS_SRC = "tensor_calls.cpp"
+
+
 def sources():
-    return sorted(f for f in os.listdir(CSRC) if f.endswith((".hip", ".cpp")))
+    return sorted(f for f in os.listdir(CSRC) if f.endswith((".hip", ".cpp")) and f != TENSOR_CALLS_SRC)
+
+
+def build_tensor_calls() -> str:
+    """Compile csrc/tensor_calls.cpp into _tensor_calls.so; returns its path."""
+    import sysconfig
+
+    import torch
+
+    base = os.path.dirname(torch.__file__)
+    tmp = TENSOR_CALLS + ".tmp"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f"-I{sysconfig.get_paths()['include']}", f"-I{base}/include", f"-I{base}/include/torch/csrc/api/include",
+           os.path.join(CSRC, TENSOR_CALLS_SRC), "-o", tmp, f"-L{base}/lib", "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed on {TENSOR_CALLS_SRC}:\n{r.stderr}")
+    os.replace(tmp, TENSOR_CALLS)
+    return TENSOR_CALLS
 
 
 def _compile(src: str, sanitize: bool = False) -> str:
@@ -150,7 +174,10 @@ def build(jobs: int | None = None, verbose: bool = False, sanitize: bool = False
     srcs = sources()
     jobs = jobs or min(len(srcs), max(1, min(os.cpu_count() or 1, 16)))
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
+        calls = None if sanitize else ex.submit(build_tensor_calls)
         objs = list(ex.map(lambda f: _compile(f, sanitize), srcs))
+        if calls is not None:
+            calls.result()
     tmp = lib + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -165,7 +192,7 @@ def build(jobs: int | None = None, verbose: bool = False, sanitize: bool = False
 def clean():
     for d in (BUILD, SAN_BUILD):
         shutil.rmtree(d, ignore_errors=True)
-    for f in (LIB, SAN_LIB):
+    for f in (LIB, SAN_LIB, TENSOR_CALLS):
         if os.path.exists(f):
             os.remove(f)
 

@@ -147,6 +147,36 @@ def library():
     return _lib()
 
 
+class _NoNative:
+    """Stands in for the native route where it is not built: every call is
+    left to the code below."""
+
+    scal = asum = dot = gemv = blackscholes = md = staticmethod(lambda *args: None)
+
+
+_NATIVE = None
+
+
+def _native():
+    """The native route of the tensor conveniences (csrc/tensor_calls.cpp):
+    its functions make an ordinary call without knobs, or return None."""
+    global _NATIVE
+    if _NATIVE is None:
+        lib, torch = _lib(), _torch()
+        with _LOCK:
+            if _NATIVE is None:
+                try:
+                    from . import _tensor_calls as native
+                except ImportError:
+                    native = _NoNative
+                else:
+                    names = ("scal", "asum", "dot", "gemv", "blackscholes", "md")
+                    at = [ctypes.cast(getattr(lib, f"lift_{n}_ex"), ctypes.c_void_p).value for n in names]
+                    native.init(*at, torch._C._cuda_getCurrentRawStream, workspace, _ok)
+                _NATIVE = native
+    return _NATIVE
+
+
 # ---------------------------------------------------------------- C entry points
 
 
@@ -385,6 +415,10 @@ def _ok(status, what):
 
 def scal(alpha, x, out=None, knobs=None):
     """out = alpha * x (binary32); ``out`` may be ``x`` for in-place."""
+    if knobs is None:
+        r = (_NATIVE or _native()).scal(alpha, x, out)
+        if r is not None:
+            return r
     torch = _torch()
     _check_tensor(x, "x", (torch.float32,))
     if out is None:
@@ -423,12 +457,20 @@ def _reduce(which, x, y, acc, result_dtype, knobs):
 
 def asum(x, acc="f32", result_dtype=None, knobs=None):
     """sum |x_i| as a 0-d device tensor (binary32 unless result_dtype=float64)."""
+    if knobs is None:
+        r = (_NATIVE or _native()).asum(x, acc, result_dtype)
+        if r is not None:
+            return r
     torch = _torch()
     return _reduce("asum", x, None, acc, result_dtype or torch.float32, knobs)
 
 
 def dot(x, y, acc="f32", result_dtype=None, knobs=None):
     """sum x_i y_i as a 0-d device tensor."""
+    if knobs is None:
+        r = (_NATIVE or _native()).dot(x, y, acc, result_dtype)
+        if r is not None:
+            return r
     torch = _torch()
     return _reduce("dot", x, y, acc, result_dtype or torch.float32, knobs)
 
@@ -436,6 +478,10 @@ def dot(x, y, acc="f32", result_dtype=None, knobs=None):
 def blackscholes(s, strike, rate, volatility, years, out=None, knobs=None):
     """map(BSComputation) over binary32 stock prices: an (n, 2) tensor of
     {call, put} per price (``out`` may be given, (n, 2) float32)."""
+    if knobs is None:
+        r = (_NATIVE or _native()).blackscholes(s, strike, rate, volatility, years, out)
+        if r is not None:
+            return r
     torch = _torch()
     _check_tensor(s, "s", (torch.float32,))
     n = s.numel()
@@ -454,6 +500,10 @@ def md(pos, nbr, cutoff, epsilon, sigma, out=None, knobs=None):
     """Forces on n particles from their neighbour lists: pos (n, 4) float32,
     nbr (n, k) int32 (outside [0, n) = empty slot); returns (n, 4) float32
     (fx, fy, fz, 0)."""
+    if knobs is None:
+        r = (_NATIVE or _native()).md(pos, nbr, cutoff, epsilon, sigma, out)
+        if r is not None:
+            return r
     torch = _torch()
     _check_tensor(pos, "pos", (torch.float32,))
     _check_tensor(nbr, "nbr", (torch.int32,))
@@ -478,6 +528,10 @@ def gemv(alpha, A, x, beta, y, acc="f32", knobs=None, lda=None):
 
     ``A`` is (m, lda) with the matrix in its first n = len(x) columns.
     """
+    if knobs is None and lda is None:
+        r = (_NATIVE or _native()).gemv(alpha, A, x, beta, y, acc)
+        if r is not None:
+            return r
     torch = _torch()
     _check_tensor(A, "A", (torch.float32, torch.bfloat16, torch.float16))
     _check_tensor(x, "x", (torch.float32,))
