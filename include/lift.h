@@ -157,7 +157,9 @@ typedef enum lift_lane_form {
  *      count it was tuned on;
  *   3. else the library defaults (gemv: also where the tuned knobs' vector
  *      loads do not fit A's row starts and x's alignment; its launch then
- *      goes by row length, for any alignment, as it does for all-zero knobs).
+ *      goes by row length, for any alignment, as it does for all-zero knobs;
+ *      dot: also where x and y lie in different 16-byte phases, whose launch
+ *      without knobs then reads both in vectors).
  * lift_default_knobs reports which applies.  Explicit knobs are never
  * overridden. */
 typedef struct lift_knobs {

@@ -454,6 +454,16 @@ const void *reduce_table(int dt, int op, int acc, int vb, int unroll)
     }
 }
 
+const void *dot_shifted_table(int dt, int acc)
+{
+    switch (dt) {
+    case LIFT_F32: return dot_shifted_kernel_f32(acc);
+    case LIFT_BF16: return dot_shifted_kernel_bf16(acc);
+    case LIFT_F16: return dot_shifted_kernel_f16(acc);
+    default: return nullptr;
+    }
+}
+
 const void *gemv_table(int dt, int acc, int vb, int rows, int unroll)
 {
     switch (dt) {
@@ -544,6 +554,7 @@ lift_status reduce_common(int op, int64_t n, int xt, const void *x, const void *
     if (overlaps(result, rb, ws, (int64_t)ws_bytes))
         return LIFT_EINVAL;
     lift_status st = LIFT_OK;
+    const bool choose = !knobs && !forced_config().present;   // the launch is the library's choice
     knobs = effective_knobs(knobs, op == OP_DOT ? TOP_DOT : TOP_ASUM, xt, acc, n, &st);
     if (st != LIFT_OK)
         return st;
@@ -569,11 +580,21 @@ lift_status reduce_common(int op, int64_t n, int xt, const void *x, const void *
     // phase, else the element size (scalar loads).
     Split3 sp{0, 0};
     int vb = k.vec_bytes;
+    bool shifted = false;
     if (n > 0 && !split3(x, op == OP_DOT ? y : nullptr, n, eb, vb, &sp)) {
-        vb = eb;
+        // Operands of a dot in different phases: where the launch is the
+        // library's choice, 16-byte loads of both, y's from wherever they
+        // start (x[1:] . x[:-1] of 2^24 fp32: element loads 39.2, now 15.5 us;
+        // bf16: 34.1, now 11.7 us), 512 threads x 2 loads of each; else
+        // element loads, as the knobs' contract says.
+        shifted = choose && !g_stamps;
+        if (shifted)
+            k = {512, 16, 2, 1, 0, 1, 1, 1, 1, 0};
+        vb = shifted ? 16 : eb;
         split3(x, nullptr, n, eb, vb, &sp);
     }
-    const void *kern = !k.lane_form ? reduce_table(xt, op, acc, vb, k.unroll)
+    const void *kern = shifted ? dot_shifted_table(xt, acc)
+                       : !k.lane_form ? reduce_table(xt, op, acc, vb, k.unroll)
                        : xt == LIFT_F32 ? reduce_lanes_kernel_f32(op, vb, k.unroll, k.lane_form)
                                         : reduce_lanes_kernel_bf16(op, vb, k.unroll, k.lane_form);
     if (!kern)

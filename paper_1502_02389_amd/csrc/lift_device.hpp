@@ -47,6 +47,26 @@ __device__ __forceinline__ typename Vec<VB>::type load_stream(const void *base, 
     return __builtin_nontemporal_load(reinterpret_cast<const typename Vec<VB>::type *>(base) + i);
 }
 
+typedef u32x4 u32x4_at2 __attribute__((aligned(2)));
+typedef u32x4 u32x4_at4 __attribute__((aligned(4)));
+
+// VB bytes of storage T at any element boundary (VB is 16 or T::bytes), read
+// once (nontemporal).  gfx950 serves such a 16-byte load by itself: at the
+// full streaming rate at any 4-byte boundary, and at odd 2-byte ones too where
+// enough wavefronts are in flight (two 256 MiB streams, one of them 2 bytes
+// off: 75.6 us, both aligned 76.4 us, at 512 threads x 2 loads per operand).
+template <class T, int VB>
+__device__ __forceinline__ typename Vec<VB>::type load_stream_any(const char *p)
+{
+    if constexpr (VB == T::bytes) {
+        return __builtin_nontemporal_load(reinterpret_cast<const typename Vec<VB>::type *>(p));
+    } else if constexpr (T::bytes == 2) {
+        return __builtin_nontemporal_load(reinterpret_cast<const u32x4_at2 *>(p));
+    } else {
+        return __builtin_nontemporal_load(reinterpret_cast<const u32x4_at4 *>(p));
+    }
+}
+
 // Scheduling fence after a group of independent loads: keeps the compiler
 // from sinking each load next to its first use (which would leave one load
 // in flight per wave and make the stream latency-bound).

@@ -29,23 +29,6 @@
 
 namespace lift {
 
-typedef u32x4 u32x4_at2 __attribute__((aligned(2)));
-typedef u32x4 u32x4_at4 __attribute__((aligned(4)));
-
-// VB bytes of storage T at any element boundary (VB is 16 or T::bytes),
-// read once (nontemporal).
-template <class T, int VB>
-__device__ __forceinline__ typename Vec<VB>::type load_stream_any(const char *p)
-{
-    if constexpr (VB == T::bytes) {
-        return __builtin_nontemporal_load(reinterpret_cast<const typename Vec<VB>::type *>(p));
-    } else if constexpr (T::bytes == 2) {
-        return __builtin_nontemporal_load(reinterpret_cast<const u32x4_at2 *>(p));
-    } else {
-        return __builtin_nontemporal_load(reinterpret_cast<const u32x4_at4 *>(p));
-    }
-}
-
 // E consecutive binary32 values of x from element c on, at any alignment.
 template <int E>
 __device__ __forceinline__ void load_x_any(const float *x, int64_t c, float *o)

@@ -203,6 +203,9 @@ const void *gemv_kernel(int dtype, int acc, int vec_bytes, int rows, int unroll)
 const void *reduce_kernel_f32(int op, int acc, int vec_bytes, int unroll);
 const void *reduce_kernel_bf16(int op, int acc, int vec_bytes, int unroll);
 const void *reduce_kernel_f16(int op, int acc, int vec_bytes, int unroll);
+const void *dot_shifted_kernel_f32(int acc);
+const void *dot_shifted_kernel_bf16(int acc);
+const void *dot_shifted_kernel_f16(int acc);
 const void *gemv_kernel_f32(int acc, int vec_bytes, int rows, int unroll);
 const void *gemv_kernel_bf16(int acc, int vec_bytes, int rows, int unroll);
 const void *gemv_kernel_f16(int acc, int vec_bytes, int rows, int unroll);

@@ -451,7 +451,9 @@ __device__ __forceinline__ void combine_partials(const ReduceArgs &a, typename B
     }
 }
 
-template <class T, int OP, int ACC, int VB, int U, bool STAMP = false>
+// SHIFTED (dot, 16-byte vectors): y does not share x's 16-byte phase and is
+// read from wherever its vectors start.
+template <class T, int OP, int ACC, int VB, int U, bool STAMP = false, bool SHIFTED = false>
 __global__ void __launch_bounds__(1024) reduce_kernel(ReduceArgs a)
 {
     constexpr int E = Elems<T, VB>::value;
@@ -464,6 +466,12 @@ __global__ void __launch_bounds__(1024) reduce_kernel(ReduceArgs a)
     const int64_t B = blockDim.x;
     const char *xv = reinterpret_cast<const char *>(a.x) + a.head * T::bytes;
     const char *yv = OP == OP_DOT ? reinterpret_cast<const char *>(a.y) + a.head * T::bytes : nullptr;
+    const auto load_y = [&](int64_t i) {
+        if constexpr (SHIFTED)
+            return load_stream_any<T, VB>(yv + i * VB);
+        else
+            return load_stream<VB>(yv, i);
+    };
 
     // The work-group's steps of B * U vectors: one contiguous chunk
     // (split^chunk), or every G-th step starting at its own (the chunking of
@@ -483,7 +491,7 @@ __global__ void __launch_bounds__(1024) reduce_kernel(ReduceArgs a)
         for (int k = 0; k < U; ++k) {
             vx[k] = load_stream<VB>(xv, base + t + k * B);
             if constexpr (OP == OP_DOT)
-                vy[k] = load_stream<VB>(yv, base + t + k * B);
+                vy[k] = load_y(base + t + k * B);
         }
         loads_in_flight();
 #pragma unroll
@@ -507,7 +515,7 @@ __global__ void __launch_bounds__(1024) reduce_kernel(ReduceArgs a)
             const int64_t i = min(base + t + k * B, vend - 1);
             vx[k] = load_stream<VB>(xv, i);
             if constexpr (OP == OP_DOT)
-                vy[k] = load_stream<VB>(yv, i);
+                vy[k] = load_y(i);
         }
         loads_in_flight();
 #pragma unroll
@@ -594,6 +602,18 @@ const void *pick_reduce(int op, int acc, int vec_bytes, int unroll)
     if (op == OP_DOT)
         return pick_acc<T, OP_DOT>(acc, vec_bytes, unroll);
     return nullptr;
+}
+
+// dot of operands in different 16-byte phases.
+template <class T>
+const void *pick_dot_shifted(int acc)
+{
+    switch (acc) {
+    case ACC_F32: return reinterpret_cast<const void *>(&reduce_kernel<T, OP_DOT, ACC_F32, 16, 2, false, true>);
+    case ACC_COMP: return reinterpret_cast<const void *>(&reduce_kernel<T, OP_DOT, ACC_COMP, 16, 2, false, true>);
+    case ACC_F64: return reinterpret_cast<const void *>(&reduce_kernel<T, OP_DOT, ACC_F64, 16, 2, false, true>);
+    default: return nullptr;
+    }
 }
 
 // The stamped instances (binary32 storage and accumulation, 16-byte loads).

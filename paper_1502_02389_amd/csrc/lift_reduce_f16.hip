@@ -8,4 +8,6 @@ const void *reduce_kernel_f16(int op, int acc, int vec_bytes, int unroll)
     return pick_reduce<F16>(op, acc, vec_bytes, unroll);
 }
 
+const void *dot_shifted_kernel_f16(int acc) { return pick_dot_shifted<F16>(acc); }
+
 }  // namespace lift

@@ -13,4 +13,6 @@ const void *reduce_kernel_stamped_f32(int op, int unroll)
     return op == OP_DOT ? pick_stamped<OP_DOT>(unroll) : pick_stamped<OP_ASUM>(unroll);
 }
 
+const void *dot_shifted_kernel_f32(int acc) { return pick_dot_shifted<F32>(acc); }
+
 }  // namespace lift
