@@ -226,18 +226,79 @@ __device__ __forceinline__ Pair wave_sum(Pair p)
     return pair_merge(pair_merge(r0, r1), pair_merge(r2, r3));
 }
 
-// binary64 butterfly over the wave (used only in the final combine).
-__device__ __forceinline__ double wave_sum(double v)
-{
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1)
-        v += __shfl_xor(v, m, 64);
-    return v;
-}
-
 __device__ __forceinline__ float merge(float a, float b) { return a + b; }
 __device__ __forceinline__ double merge(double a, double b) { return a + b; }
 __device__ __forceinline__ Pair merge(Pair a, Pair b) { return pair_merge(a, b); }
+
+// One butterfly step over lanes S apart (S = 1 .. 32, all smaller steps
+// done): both sides get the same bits, merge being symmetric.
+template <int S>
+__device__ __forceinline__ void swap_words(uint32_t v, uint32_t &a, uint32_t &b)
+{
+    if constexpr (S < 16) {
+        constexpr int ctrl = S == 1 ? DPP_QUAD_XOR1 : S == 2 ? DPP_QUAD_XOR2 : S == 4 ? DPP_HALF_MIRROR : DPP_ROW_MIRROR;
+        a = v;
+        b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xf, 0xf, false);
+    } else if constexpr (S == 16) {  // rows 0 <-> 1 and 2 <-> 3
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        a = r[0];
+        b = r[1];
+    } else {  // the wave's halves
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        a = r[0];
+        b = r[1];
+    }
+}
+
+template <int S>
+__device__ __forceinline__ float butterfly(float v)
+{
+    uint32_t a, b;
+    swap_words<S>(__builtin_bit_cast(uint32_t, v), a, b);
+    return merge(bits_to_float(a), bits_to_float(b));
+}
+
+template <int S>
+__device__ __forceinline__ Pair butterfly(Pair v)
+{
+    uint32_t sa, sb, ca, cb;
+    swap_words<S>(__builtin_bit_cast(uint32_t, v.s), sa, sb);
+    swap_words<S>(__builtin_bit_cast(uint32_t, v.c), ca, cb);
+    return merge(Pair{bits_to_float(sa), bits_to_float(ca)}, Pair{bits_to_float(sb), bits_to_float(cb)});
+}
+
+template <int S>
+__device__ __forceinline__ double butterfly(double v)
+{
+    const uint64_t w = __builtin_bit_cast(uint64_t, v);
+    uint32_t la, lb, ha, hb;
+    swap_words<S>((uint32_t)w, la, lb);
+    swap_words<S>((uint32_t)(w >> 32), ha, hb);
+    return merge(__builtin_bit_cast(double, ((uint64_t)ha << 32) | la),
+                 __builtin_bit_cast(double, ((uint64_t)hb << 32) | lb));
+}
+
+// Sum over each aligned group of L lanes; every lane of a group gets it.
+template <int L, class A>
+__device__ __forceinline__ A lanes_sum(A v)
+{
+    if constexpr (L >= 2)
+        v = butterfly<1>(v);
+    if constexpr (L >= 4)
+        v = butterfly<2>(v);
+    if constexpr (L >= 8)
+        v = butterfly<4>(v);
+    if constexpr (L >= 16)
+        v = butterfly<8>(v);
+    if constexpr (L >= 32)
+        v = butterfly<16>(v);
+    if constexpr (L >= 64)
+        v = butterfly<32>(v);
+    return v;
+}
+
+// binary64 sum over the 64 lanes, every lane gets it.
+__device__ __forceinline__ double wave_sum(double v) { return lanes_sum<64>(v); }
 
 // Work-group reduction: wave butterflies, one LDS slot per wave, then the
 // wave totals folded in wave order by thread 0.  The value is valid in

@@ -48,73 +48,6 @@ __device__ __forceinline__ void load_x_any(const float *x, int64_t c, float *o)
     }
 }
 
-// One butterfly step over lanes S apart (S = 1 .. 32, all smaller steps
-// done): both sides get the same bits, merge being symmetric.
-template <int S>
-__device__ __forceinline__ void swap_words(uint32_t v, uint32_t &a, uint32_t &b)
-{
-    if constexpr (S < 16) {
-        constexpr int ctrl = S == 1 ? DPP_QUAD_XOR1 : S == 2 ? DPP_QUAD_XOR2 : S == 4 ? DPP_HALF_MIRROR : DPP_ROW_MIRROR;
-        a = v;
-        b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xf, 0xf, false);
-    } else if constexpr (S == 16) {  // rows 0 <-> 1 and 2 <-> 3
-        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-        a = r[0];
-        b = r[1];
-    } else {  // the wave's halves
-        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-        a = r[0];
-        b = r[1];
-    }
-}
-
-template <int S>
-__device__ __forceinline__ float butterfly(float v)
-{
-    uint32_t a, b;
-    swap_words<S>(__builtin_bit_cast(uint32_t, v), a, b);
-    return merge(bits_to_float(a), bits_to_float(b));
-}
-
-template <int S>
-__device__ __forceinline__ Pair butterfly(Pair v)
-{
-    uint32_t sa, sb, ca, cb;
-    swap_words<S>(__builtin_bit_cast(uint32_t, v.s), sa, sb);
-    swap_words<S>(__builtin_bit_cast(uint32_t, v.c), ca, cb);
-    return merge(Pair{bits_to_float(sa), bits_to_float(ca)}, Pair{bits_to_float(sb), bits_to_float(cb)});
-}
-
-template <int S>
-__device__ __forceinline__ double butterfly(double v)
-{
-    const uint64_t w = __builtin_bit_cast(uint64_t, v);
-    uint32_t la, lb, ha, hb;
-    swap_words<S>((uint32_t)w, la, lb);
-    swap_words<S>((uint32_t)(w >> 32), ha, hb);
-    return merge(__builtin_bit_cast(double, ((uint64_t)ha << 32) | la),
-                 __builtin_bit_cast(double, ((uint64_t)hb << 32) | lb));
-}
-
-// Sum over each aligned group of L lanes; every lane of a group gets it.
-template <int L, class A>
-__device__ __forceinline__ A lanes_sum(A v)
-{
-    if constexpr (L >= 2)
-        v = butterfly<1>(v);
-    if constexpr (L >= 4)
-        v = butterfly<2>(v);
-    if constexpr (L >= 8)
-        v = butterfly<4>(v);
-    if constexpr (L >= 16)
-        v = butterfly<8>(v);
-    if constexpr (L >= 32)
-        v = butterfly<16>(v);
-    if constexpr (L >= 64)
-        v = butterfly<32>(v);
-    return v;
-}
-
 // y_i from the row's finished dot, y_i read before (`yold`).
 template <int ACC>
 __device__ __forceinline__ float row_epilogue(RowPartT<ACC> d, float alpha, float beta, float yold)

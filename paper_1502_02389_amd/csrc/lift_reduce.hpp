@@ -405,8 +405,8 @@ __device__ __forceinline__ void fold_slots(char *ws, int64_t last, ST own, ST &v
 // own device-scope request), hence one word per partial and 4 loads per lane
 // where they do: with two words per partial the compensated form gained
 // nothing, and re-reading only what is missing lost what fp32 had gained.
-template <int ACC, bool STAMP>
-__device__ __forceinline__ void combine_partials(const ReduceArgs &a, typename BlockT<ACC>::type wg)
+template <int ACC, bool STAMP, class W>
+__device__ __forceinline__ void combine_partials(const ReduceArgs &a, W wg)
 {
     using ST = typename SlotT<ACC>::type;
     const int t = threadIdx.x;
@@ -424,7 +424,7 @@ __device__ __forceinline__ void combine_partials(const ReduceArgs &a, typename B
         return;
     char *ws = reinterpret_cast<char *>(a.ws);
     const int64_t last = (int64_t)gridDim.x - 1;
-    ST own = to_slot<ACC>(wg);
+    ST own = ST(wg);
     if (blockIdx.x != last) {
         if (t == 0) {
             store_word(slot_word(ws, blockIdx.x), to_word(own));
@@ -452,7 +452,8 @@ __device__ __forceinline__ void combine_partials(const ReduceArgs &a, typename B
 }
 
 // SHIFTED (dot, 16-byte vectors): y does not share x's 16-byte phase and is
-// read from wherever its vectors start.
+// read from wherever its vectors start; the lanes' binary32 sums meet in
+// binary64 (a dot that cancels loses nothing in the trees).
 template <class T, int OP, int ACC, int VB, int U, bool STAMP = false, bool SHIFTED = false>
 __global__ void __launch_bounds__(1024) reduce_kernel(ReduceArgs a)
 {
@@ -550,9 +551,14 @@ __global__ void __launch_bounds__(1024) reduce_kernel(ReduceArgs a)
         stamp<STAMP>(a, 1);
         __builtin_amdgcn_sched_barrier(0);
     }
-    BT wg = block_sum<BT>(acc.value(), lds_block);
-    stamp<STAMP>(a, 2);
-    combine_partials<ACC, STAMP>(a, wg);
+    if constexpr (SHIFTED && ACC != ACC_COMP) {
+        __shared__ double lds_wide[16];
+        combine_partials<ACC_F64, STAMP>(a, block_sum<double>((double)acc.value(), lds_wide));
+    } else {
+        BT wg = block_sum<BT>(acc.value(), lds_block);
+        stamp<STAMP>(a, 2);
+        combine_partials<ACC, STAMP>(a, wg);
+    }
 }
 
 // Table of instantiated reduce kernels for storage T.
