@@ -358,7 +358,13 @@ lift_status lift_md_ex(int64_t n, const float *pos, int64_t k, const int32_t *nb
  * and E copies of x, each padded to a multiple of 4 floats, fitting in
  * 16320 floats of LDS, each row from its own start: scalars up to its first
  * vec_bytes boundary, then vectors, then the scalar tail (a wavefront takes
- * two rows E apart, which start alike); else with element loads. */
+ * two rows E apart, which start alike); else with element loads.
+ *
+ * Without knobs a batch that reads at most 64 KiB per wavefront of the device
+ * (268 MB on 256 compute units) is one launch instead, of tiles that one
+ * wavefront each takes, every row and vector read from where it starts; a
+ * larger one runs as above with reduction tiles of a quarter of a
+ * work-group's share (at least 65536 elements, at most the tuned split). */
 typedef enum lift_kind {
     LIFT_KIND_ASUM = 0,
     LIFT_KIND_DOT = 1,
@@ -397,13 +403,14 @@ lift_status lift_batch_create(const lift_problem *probs, int32_t count, lift_dty
                               lift_batch **out);
 
 /* Enqueue the whole batch on `stream`: the reduction launch, then the gemv
- * launch (either is skipped when the batch has no tiles of its kind).
+ * launch (either is skipped when the batch has no tiles of its kind), or the
+ * one launch of wavefront tiles.
  * Allocation-free and memset-free: each kernel leaves its counters reset, so
  * the call can be captured into a HIP graph and replayed.  Runs of one batch
  * must not overlap (they share the counters).  An armed timing hook
  * (lift_time_next_launch) spans the whole run: start with the first launch,
  * stop with the last; an armed stamp hook (lift_stamp_next_launch) makes
- * both launches stamped. */
+ * every launch stamped. */
 lift_status lift_batch_run(lift_batch *batch, hipStream_t stream);
 
 /* Capture lift_batch_run on `stream` (which must not be the null stream)

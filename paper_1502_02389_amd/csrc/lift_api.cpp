@@ -1004,9 +1004,253 @@ struct lift_batch {
     BatchArgs args[2]{};
     hipEvent_t ev[2] = {nullptr, nullptr};  // inner ends of a timed two-launch run
     int storage = 0, acc = 0, vb = 0, unroll = 0;  // for the stamped gemv instance
+    bool waves = false;       // one launch of wavefront tiles (grid[0], kern[0], wave_args)
+    BatchWaveArgs wave_args{};
 };
 
 namespace {
+
+const void *batch_wave_table(int dt, int acc, bool stamped)
+{
+    switch (dt) {
+    case LIFT_F32: return batch_wave_f32(acc, stamped);
+    case LIFT_BF16: return batch_wave_bf16(acc, stamped);
+    case LIFT_F16: return batch_wave_f16(acc, stamped);
+    default: return nullptr;
+    }
+}
+
+// Work-groups of the wavefront kernel that the device holds, a multiple of
+// DRAW_LISTS.
+lift_status batch_wave_groups(int storage, int acc, const void **kern, int64_t *groups)
+{
+    *kern = batch_wave_table(storage, acc, false);
+    if (!*kern)
+        return LIFT_EUNSUPPORTED;
+    int cus = 0, fit = 1;
+    lift_status st = cu_count(&cus);
+    if (st == LIFT_OK)
+        st = resident_per_cu(*kern, 256, &fit);
+    *groups = std::max<int64_t>(DRAW_LISTS, (int64_t)cus * std::min(fit, 4) / DRAW_LISTS * DRAW_LISTS);
+    return st;
+}
+
+// Bytes of x, y and A that a batch reads, and the problems that read any.
+double batch_reads(const lift_problem *probs, int32_t count, int64_t eb, int64_t *filled)
+{
+    double total = 0;
+    *filled = 0;
+    for (int32_t i = 0; i < count; ++i) {
+        const lift_problem &q = probs[i];
+        const double n = (double)q.n * eb * (q.kind == LIFT_KIND_GEMV ? (double)q.m : q.kind == LIFT_KIND_DOT ? 2 : 1);
+        total += std::max(0.0, n);
+        *filled += n > 0;
+    }
+    return total;
+}
+
+// Up to this many bytes per wavefront (268 MB on 256 CUs) a batch without
+// knobs runs as wavefront tiles, above it as the two launches of work-group
+// tiles.  Measured in us, two launches | wavefronts: 1.8 MB bf16 13.4 | 7.3,
+// 94 MB f32 108 | 18, 163 MB bf16 102 | 30, 180 MB of f32 gemv 44 | 43, 194 MB
+// bf16 50 | 38; but 301 MB of bf16 gemv 66 | 83, 332 MB of f32 gemv 68 | 81,
+// 1.57 GB f32 250 | 303, 3.7 GB bf16 630 | 682: independent wavefronts that
+// draw their tiles stream at 5.2 to 5.5 TB/s, work-groups at 5.9 to 6.5.
+constexpr double BATCH_WAVE_SHARE = 65536;
+
+// The library's choice for a batch without knobs: wavefront tiles or (false)
+// work-group tiles, then with *red_split elements per reduction tile.
+//
+// A work-group takes 70 us for a tile of 4 MB, so with the largest tile that
+// the default gives, a batch of some 100 MB ends on one.  A quarter of a
+// work-group's share (2 per CU) evens that out; below 65536 elements the cost
+// per tile shows (3.7 GB bf16: 624 us at 2^20, 645 at 65536, 673 at 32768).
+// At the default split and with this, us: 314 MB f32 111 | 63, 514 MB bf16
+// 160 | 102, 645 MB f32 181 | 117, 1.47 GB f32 243 | 235.
+bool batch_choose(const lift_problem *probs, int32_t count, int storage, int acc, int64_t *red_split)
+{
+    const void *kern = nullptr;
+    int64_t groups = 0, filled = 0;
+    int cus = 0;
+    if (batch_wave_groups(storage, acc, &kern, &groups) != LIFT_OK || cu_count(&cus) != LIFT_OK)
+        return false;  // no device: the plan itself reports that
+    const int eb = elem_bytes(storage);
+    const double total = batch_reads(probs, count, eb, &filled);
+    if (total <= BATCH_WAVE_SHARE * 4 * groups)
+        return true;
+    *red_split = std::min(*red_split, (int64_t)std::max(65536.0, std::min(1e15, total / (2 * cus) / 4 / eb)));
+    return false;
+}
+
+// The plan of a batch without knobs (lift_batch_wave.hpp), its problems
+// already checked.
+//
+// Tile size (bytes of x, y and A): what gives every wavefront about one tile
+// (problems shorter than that leave more tiles than wavefronts, which are then
+// drawn).  Never below 8 KiB, one step of loads.
+lift_status batch_plan_waves(const lift_problem *probs, int32_t count, int storage, int acc, int rt, int64_t bytes,
+                             lift_batch *b)
+{
+    const int64_t eb = elem_bytes(storage), e = 16 / eb;
+    const void *kern = nullptr;
+    int64_t most = 0, filled = 0;
+    lift_status st = batch_wave_groups(storage, acc, &kern, &most);
+    if (st != LIFT_OK)
+        return st;
+    const int64_t waves = most * 4;
+    const double total = batch_reads(probs, count, eb, &filled);
+    const int64_t tile = (int64_t)std::max(8192.0, total / std::max<int64_t>(waves / 2, waves - filled));
+
+    struct Planned {
+        WaveTile t;
+        int64_t cost;
+    };
+    std::vector<Planned> tiles;
+    int64_t slots = 0, kinds[2] = {0, 0};
+    for (int32_t i = 0; i < count; ++i) {
+        const lift_problem &q = probs[i];
+        Planned p;
+        std::memset(&p, 0, sizeof p);
+        p.t.kind = q.kind;
+        p.t.problem = i;
+        p.t.alpha = q.alpha;
+        p.t.beta = q.beta;
+        if (q.kind == LIFT_KIND_GEMV) {
+            if (q.m == 0)
+                continue;
+            if (q.n > INT32_MAX)
+                return LIFT_EUNSUPPORTED;
+            // whole groups of the rows that a wavefront has in flight: 4 x 64 / L
+            // side by side for rows of L <= 64 vectors
+            const int64_t vecs = (q.n + e - 1) / e;
+            int64_t lanes = 8;
+            while (lanes < 64 && lanes < vecs)
+                lanes *= 2;
+            const int64_t unit = vecs <= 64 ? 4 * 64 / lanes : 4;
+            const int64_t want = std::max<int64_t>(unit, tile / std::max<int64_t>(1, q.n * eb));
+            const int64_t nt = (q.m + want - 1) / want;
+            int64_t rows = (q.m + nt - 1) / nt;
+            rows = std::min<int64_t>((rows + unit - 1) / unit * unit, 1 << 30);
+            for (int64_t r = 0; r < q.m; r += rows) {
+                p.t.a = static_cast<const char *>(q.a) + r * q.lda * eb;
+                p.t.b = q.b;
+                p.t.out = static_cast<float *>(q.out) + r;
+                p.t.pitch = q.lda * eb;
+                p.t.n = (int32_t)q.n;
+                p.t.rows = (int32_t)std::min(rows, q.m - r);
+                p.t.ntiles = 1;
+                p.cost = p.t.rows * q.n * eb + 4096;
+                tiles.push_back(p);
+                ++kinds[1];
+            }
+        } else {
+            const int64_t streams = q.kind == LIFT_KIND_DOT ? 2 : 1;
+            const int64_t want = std::max<int64_t>(64 * e, tile / (eb * streams));
+            int64_t nt = std::max<int64_t>(1, (q.n + want - 1) / want);
+            int64_t len = (q.n + nt - 1) / nt;
+            len = std::min<int64_t>(std::max<int64_t>(64 * e, (len + 64 * e - 1) / (64 * e) * (64 * e)), 1 << 30);
+            nt = std::max<int64_t>(1, (q.n + len - 1) / len);
+            if (slots + nt > INT32_MAX)
+                return LIFT_EUNSUPPORTED;
+            for (int64_t k = 0; k < nt; ++k) {
+                const int64_t at = k * len;
+                p.t.a = q.n ? static_cast<const char *>(q.a) + at * eb : nullptr;
+                p.t.b = q.n && streams == 2 ? static_cast<const char *>(q.b) + at * eb : nullptr;
+                p.t.out = q.out;
+                p.t.n = (int32_t)std::min(len, q.n - at);
+                p.t.rows = (int32_t)k;
+                p.t.ntiles = (int32_t)nt;
+                p.t.slot = (int32_t)(slots + k);
+                p.cost = p.t.n * eb * streams + 4096;
+                tiles.push_back(p);
+                ++kinds[0];
+            }
+            slots += nt;
+        }
+    }
+    if ((int64_t)tiles.size() >= 1 << 30)
+        return LIFT_EUNSUPPORTED;
+    std::stable_sort(tiles.begin(), tiles.end(), [](const Planned &x, const Planned &y) { return x.cost > y.cost; });
+    const int64_t ntiles = (int64_t)tiles.size();
+    const int64_t grid = std::min<int64_t>(most, (std::max<int64_t>(ntiles, 1) + DRAW_LISTS - 1) / DRAW_LISTS * DRAW_LISTS);
+    std::vector<WaveTile> table((size_t)ntiles);
+    std::vector<int32_t> records((size_t)ntiles);   // stamps: the reductions' tiles first, then gemv's
+    int64_t at[2] = {0, kinds[0]};
+    for (int64_t i = 0; i < ntiles; ++i) {
+        table[(size_t)i] = tiles[(size_t)i].t;
+        records[(size_t)i] = (int32_t)at[table[(size_t)i].kind == LIFT_KIND_GEMV]++;
+    }
+
+    int dev = 0;
+    hipError_t he = hipGetDevice(&dev);
+    if (he != hipSuccess)
+        return hip_fail(he);
+    // one allocation: draw counters | counter and groups of work-groups that
+    // left | per-problem counters | tiles | records | slots
+    auto up = [](int64_t v) { return (v + 255) / 256 * 256; };
+    const int64_t off_done = up(DRAW_LISTS * WS_GROUP_STRIDE), off_groups = off_done + 256;
+    const int64_t off_pc = off_groups + up((grid + ARRIVAL_GROUP - 1) / ARRIVAL_GROUP * WS_GROUP_STRIDE);
+    const int64_t off_ti = off_pc + up(std::max<int64_t>(count, 1) * 4);
+    const int64_t off_re = off_ti + up(std::max<int64_t>(ntiles, 1) * (int64_t)sizeof(WaveTile));
+    const int64_t off_sl = off_re + up(std::max<int64_t>(ntiles, 1) * 4);
+    void *mem = nullptr;
+    he = hipMalloc(&mem, (size_t)(off_sl + std::max<int64_t>(slots, 1) * WS_SLOT));
+    if (he != hipSuccess)
+        return hip_fail(he);
+    char *base = static_cast<char *>(mem);
+    if ((he = hipMemset(base, 0, (size_t)off_ti)) != hipSuccess ||
+        (ntiles > 0 && ((he = hipMemcpy(base + off_ti, table.data(), table.size() * sizeof(WaveTile),
+                                        hipMemcpyHostToDevice)) != hipSuccess ||
+                        (he = hipMemcpy(base + off_re, records.data(), records.size() * 4, hipMemcpyHostToDevice)) !=
+                            hipSuccess))) {
+        hipFree(mem);
+        return hip_fail(he);
+    }
+    b->device = dev;
+    b->storage = storage;
+    b->acc = acc;
+    b->nprobs = count;
+    b->bytes = bytes;
+    b->block = 256;
+    b->dmem = mem;
+    b->waves = true;
+    b->ntiles[0] = kinds[0];
+    b->ntiles[1] = kinds[1];
+    b->grid[0] = grid;
+    b->kern[0] = kern;
+    BatchWaveArgs &a = b->wave_args;
+    a.tiles = reinterpret_cast<const WaveTile *>(base + off_ti);
+    a.ntiles = (int32_t)ntiles;
+    a.lists = base;
+    a.done = reinterpret_cast<unsigned *>(base + off_done);
+    a.groups = base + off_groups;
+    a.pcount = reinterpret_cast<unsigned *>(base + off_pc);
+    a.slots = base + off_sl;
+    a.result_f64 = rt == LIFT_F64;
+    a.dynamic = ntiles > grid * 4;
+    a.records = reinterpret_cast<const int32_t *>(base + off_re);
+    return LIFT_OK;
+}
+
+// One run of such a plan; an armed stamp hook takes the stamped instance.
+lift_status batch_run_waves(lift_batch *b, hipStream_t stream)
+{
+    BatchWaveArgs a = b->wave_args;
+    const void *kern = b->kern[0];
+    if (g_stamps) {
+        a.stamps = g_stamps;
+        const int64_t cap = g_stamp_capacity;
+        g_stamps = nullptr;
+        if (b->acc != LIFT_ACC_F32 || (b->storage != LIFT_F32 && b->storage != LIFT_BF16))
+            return LIFT_EUNSUPPORTED;
+        if (a.ntiles > cap)
+            return LIFT_EINVAL;
+        kern = batch_wave_table(b->storage, b->acc, true);
+        if (!kern)
+            return LIFT_EUNSUPPORTED;
+    }
+    return launch(kern, b->grid[0], b->block, &a, stream);
+}
 
 lift_status batch_plan(const lift_problem *probs, int32_t count, int storage, int acc, int rt,
                        const lift_knobs *knobs, lift_batch *b)
@@ -1021,6 +1265,7 @@ lift_status batch_plan(const lift_problem *probs, int32_t count, int storage, in
         return LIFT_EINVAL;
     const int eb = elem_bytes(storage), rb = elem_bytes(rt);
     lift_status st = LIFT_OK;
+    const bool unset = !knobs && !forced_config().present;   // the plan is the library's choice
     knobs = effective_knobs(knobs, TOP_BATCH, storage, acc, 0, &st);
     if (st != LIFT_OK)
         return st;
@@ -1036,6 +1281,8 @@ lift_status batch_plan(const lift_problem *probs, int32_t count, int storage, in
         return LIFT_EUNSUPPORTED;  // batch gemv tiles use one wavefront per row pair
     const int vb = k.vec_bytes;
     const int64_t e = vb / eb;
+    int64_t red_split = k.split;
+    const bool choose = unset && batch_choose(probs, count, storage, acc, &red_split);   // wavefront tiles
 
     std::vector<std::pair<uintptr_t, uintptr_t>> outs, ins;
     std::vector<BatchProblem> hp((size_t)count);
@@ -1081,7 +1328,7 @@ lift_status batch_plan(const lift_problem *probs, int32_t count, int storage, in
             p.head = sp.head;
             p.nvec = sp.nvec;
             // tile length in units (vectors or elements), whole steps
-            int64_t len = std::max<int64_t>(1, (k.split + unit_e - 1) / unit_e);
+            int64_t len = std::max<int64_t>(1, (red_split + unit_e - 1) / unit_e);
             len = (len + step - 1) / step * step;
             const int64_t nt = std::max<int64_t>(1, (p.nvec + len - 1) / len);
             if (nt > INT32_MAX)
@@ -1089,7 +1336,7 @@ lift_status batch_plan(const lift_problem *probs, int32_t count, int storage, in
             p.ntiles = (int32_t)nt;
             p.slot_base = slots;
             slots += nt;
-            for (int64_t t = 0; t < nt; ++t) {
+            for (int64_t t = 0; t < nt && !choose; ++t) {
                 BatchTile tl{i, (int32_t)t, t * len, std::min(len, p.nvec - t * len)};
                 if (tl.len < 0)
                     tl.len = 0;
@@ -1131,7 +1378,7 @@ lift_status batch_plan(const lift_problem *probs, int32_t count, int storage, in
             if (nt > INT32_MAX)
                 return LIFT_EUNSUPPORTED;
             p.ntiles = (int32_t)nt;
-            for (int64_t t = 0; t < nt; ++t) {
+            for (int64_t t = 0; t < nt && !choose; ++t) {
                 BatchTile tl{i, (int32_t)t, t * rows, std::min(rows, q.m - t * rows)};
                 tiles[1].push_back(tl);
                 // a row shorter than one step of loads costs about a whole step
@@ -1144,6 +1391,8 @@ lift_status batch_plan(const lift_problem *probs, int32_t count, int storage, in
     }
     if (any_overlap(outs, ins))
         return LIFT_EINVAL;
+    if (choose)
+        return batch_plan_waves(probs, count, storage, acc, rt, bytes, b);
     if ((int64_t)tiles[0].size() > INT32_MAX || (int64_t)tiles[1].size() > INT32_MAX || count > 0x7fffffff)
         return LIFT_EUNSUPPORTED;
 
@@ -1628,6 +1877,8 @@ lift_status lift_batch_run(lift_batch *b, hipStream_t stream)
         return hip_fail(e);
     if (dev != b->device)
         return LIFT_EINVAL;
+    if (b->waves)
+        return batch_run_waves(b, stream);
     // An armed timing hook covers the whole run: its start event goes with
     // the first launch and its stop event with the last (the batch's own
     // pair of events fills the other ends when there are two launches).
@@ -1714,7 +1965,8 @@ lift_status lift_batch_info(const lift_batch *b, int64_t *tiles, int64_t *grid, 
     if (tiles)
         *tiles = b->ntiles[0] + b->ntiles[1];
     if (grid)
-        *grid = (b->ntiles[0] ? b->grid[0] : 0) + (b->ntiles[1] ? b->grid[1] : 0);
+        *grid = b->waves ? (b->ntiles[0] + b->ntiles[1] ? b->grid[0] : 0)
+                         : (b->ntiles[0] ? b->grid[0] : 0) + (b->ntiles[1] ? b->grid[1] : 0);
     if (bytes)
         *bytes = b->bytes;
     return LIFT_OK;

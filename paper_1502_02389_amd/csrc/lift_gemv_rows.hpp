@@ -76,26 +76,35 @@ __device__ __forceinline__ int row_head(const void *A, int64_t lda, int64_t row)
 }
 
 // A lane's columns of every row it meets: V vectors of E columns, vector k
-// from column head + (sub + L k) E on, moved back to end at the row's last
-// column where it would pass it.  skip = leading elements of the (moved)
-// vector that belong to the vector before; E = none of them is the lane's.
-template <class T, int ACC, int VB, int V>
+// from column head + (sub + L k) E on.  The row has more than L WHOLE vectors
+// (by default all but a lane's last: V is the smallest that covers the row),
+// so the first WHOLE of every lane are whole; a later one that would pass the
+// row's last column is moved back to end there, and its leading elements that
+// belong to the vector before (all, past the row) count as zeros.  Byte
+// offsets are 32-bit (a row whose x the registers hold is short), which with a
+// wave-uniform row leaves the address to the scalar unit.
+template <class T, int ACC, int VB, int V, int WHOLE = V - 1>
 struct LaneCols {
     static constexpr int E = Elems<T, VB>::value;
-    int64_t at[V];   // byte offset of vector k in its row
-    int skip[V];
+    uint32_t first, step;   // byte offset of vector 0 in a row, distance between vectors
+    uint32_t end;           // of the last place where a vector fits
     float x[V][E];
 
-    __device__ __forceinline__ void set(const float *xs, int64_t n, int head, int sub, int L)
+    // vector k's byte offset, and how many of its leading elements to skip
+    __device__ __forceinline__ uint32_t at(int k) const
     {
+        return k < WHOLE ? first + k * step : min(first + k * step, end);
+    }
+    __device__ __forceinline__ int skip(int k) const { return (int)((first + k * step - at(k)) / T::bytes); }
+
+    __device__ __forceinline__ void set(const float *xs, int64_t n, int head, int sub, int L)   // n >= E
+    {
+        first = (uint32_t)(head + sub * E) * T::bytes;
+        step = (uint32_t)L * VB;
+        end = (uint32_t)(n - E) * T::bytes;
 #pragma unroll
-        for (int k = 0; k < V; ++k) {
-            const int64_t c0 = head + ((int64_t)sub + (int64_t)L * k) * E;
-            const int64_t c = c0 + E <= n ? c0 : n - E;   // n >= E (host)
-            skip[k] = (int)(c0 - c < E ? c0 - c : E);
-            at[k] = c * T::bytes;
-            load_x_any<E>(xs, c, x[k]);
-        }
+        for (int k = 0; k < V; ++k)
+            load_x_any<E>(xs, at(k) / T::bytes, x[k]);
     }
     // Zeros for the elements of x that are not the lane's.  Called once, after
     // the first rows' loads are issued, so that they do not wait for x
@@ -104,20 +113,20 @@ struct LaneCols {
     __device__ __forceinline__ void mask()
     {
 #pragma unroll
-        for (int e = 0; e < E; ++e)
-            x[V - 1][e] = e >= skip[V - 1] ? x[V - 1][e] : 0.f;
+        for (int k = WHOLE; k < V; ++k)
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                x[k][e] = e >= skip(k) ? x[k][e] : 0.f;
     }
-    // The row's terms of vector k (loaded as v), into acc.  The host picks
-    // the smallest V that covers the row, so every vector but a lane's last
-    // is whole.
+    // The row's terms of vector k (loaded as v), into acc.
     __device__ __forceinline__ void add(RowAcc<ACC, E> &acc, int k, const typename Vec<VB>::type &v) const
     {
         float a[E];
         decode<T, VB>(v, a);
-        if (k == V - 1) {
+        if (k >= WHOLE) {
 #pragma unroll
             for (int e = 0; e < E; ++e)
-                a[e] = e >= skip[k] ? a[e] : 0.f;
+                a[e] = e >= skip(k) ? a[e] : 0.f;
         }
         acc.add(a, x[k]);
     }
@@ -173,7 +182,7 @@ __global__ void __launch_bounds__(256) gemv_rows_kernel(GemvRowsArgs a)
         for (int i = 0; i < R; ++i)
 #pragma unroll
             for (int k = 0; k < V; ++k)
-                v[i][k] = load_stream_any<T, VB>(row[i] + cols.at[k]);
+                v[i][k] = load_stream_any<T, VB>(row[i] + cols.at(k));
         if (mine) {  // one lane per row: a load by all of them costs as much as a vector
 #pragma unroll
             for (int i = 0; i < R; ++i)
@@ -240,7 +249,7 @@ __global__ void __launch_bounds__(512) gemv_rows_wg_kernel(GemvRowsArgs a)
         const char *row = reinterpret_cast<const char *>(a.A) + r * pitch;
 #pragma unroll
         for (int k = 0; k < V; ++k)
-            v[k] = load_stream_any<T, VB>(row + cols.at[k]);
+            v[k] = load_stream_any<T, VB>(row + cols.at(k));
         if (mine)
             h = *reinterpret_cast<const typename T::raw *>(row);
         if (t == j % PARK && a.beta != 0.f)

@@ -179,6 +179,48 @@ struct BatchArgs {
     uint64_t *stamps;     // stamped instances only: STAMPS_PER_TILE words per tile
 };
 
+// ---- batched form without knobs (lift_batch_wave.hpp) -----------------------
+
+// One tile of one wavefront.  Reductions: n elements of x = a (and y = b) for
+// the result out; of a problem of several tiles, this one's partial goes to
+// `slot` and rows is its number in the problem.  gemv: `rows` rows of n
+// columns from a on, `pitch` bytes apart, x = b, y = out.
+struct WaveTile {
+    const void *a;
+    const void *b;
+    void *out;
+    int64_t pitch;
+    int32_t kind;
+    int32_t n;
+    int32_t rows;
+    int32_t ntiles;
+    int32_t slot;
+    int32_t problem;
+    float alpha;
+    float beta;
+};
+static_assert(sizeof(WaveTile) == 64, "the kernel reads it as 16 words");
+
+constexpr int DRAW_LISTS = 8;
+
+struct BatchWaveArgs {
+    const WaveTile *tiles;
+    int32_t ntiles;       // below 2^30
+    char *lists;          // DRAW_LISTS counters of drawn tiles, WS_GROUP_STRIDE apart
+    unsigned *done;       // groups of work-groups that have left (arrive())
+    char *groups;
+    unsigned *pcount;     // per problem: tiles finished
+    char *slots;
+    int32_t result_f64;
+    int32_t dynamic;      // more tiles than wavefronts: draw
+    const int32_t *records;  // stamped instances: a tile's place in `stamps`
+    uint64_t *stamps;
+};
+
+const void *batch_wave_f32(int acc, bool stamped);
+const void *batch_wave_bf16(int acc, bool stamped);
+const void *batch_wave_f16(int acc, bool stamped);
+
 // Clock readings of a stamped batch launch, per tile (indexed by its place
 // in that launch's tile table): [0] the work-group starts the tile, [1] it
 // is done with it, [2] the tile's problem (high 32 bits) and length (low
