@@ -444,6 +444,24 @@ int64_t chunk_for(int64_t nvec, int64_t elems_per_vec, const Knobs &k, int cus, 
     return chunk;
 }
 
+// Loads in flight per thread of a reduction whose launch is the library's
+// choice: as few as let every work-group take one step on a compute unit of
+// its own.  A vector that one work-group covers stays with it (there is no
+// combine then: 16384 bf16 2.3 us against 2.7 to 2.8 over several).
+//
+// Replayed from a graph, us, at the fixed 8 (asum) or 4 (dot) loads and now:
+// 2^16 fp32 asum 2.90 | 2.66, 2^18 fp32 3.32 | 2.97, 2^18 bf16 3.41 | 2.82, 2^20
+// bf16 3.63 | 3.19; dot 2^18 bf16 3.54 | 2.89, 2^19 fp32 3.78 | 3.38.  One step
+// more than that on a compute unit costs a round trip: 2^20 fp32 asum with 2
+// loads 3.86, with 4 3.61.
+int spread_unroll(int64_t nvec, int block, int unroll, int cus)
+{
+    const auto groups = [&](int u) { return (nvec + (int64_t)block * u - 1) / ((int64_t)block * u); };
+    while (unroll > 1 && groups(unroll) > 1 && groups(unroll / 2) <= cus)
+        unroll /= 2;
+    return unroll;
+}
+
 const void *reduce_table(int dt, int op, int acc, int vb, int unroll)
 {
     switch (dt) {
@@ -593,13 +611,23 @@ lift_status reduce_common(int op, int64_t n, int xt, const void *x, const void *
         vb = shifted ? 16 : eb;
         split3(x, nullptr, n, eb, vb, &sp);
     }
+    int cus = 0;
+    // Only where the order of the binary32 sums does not matter beyond the last
+    // digit: asum (no cancellation) to a binary32 result, and compensated sums.
+    // A dot's binary32 sums keep theirs, and so does a binary64 result.
+    if (choose && !knobs && vb == 16 && !shifted &&
+        (acc == LIFT_ACC_F32_COMP || (op == OP_ASUM && rt == LIFT_F32))) {
+        st = cu_count(&cus);
+        if (st != LIFT_OK)
+            return st;
+        k.unroll = spread_unroll(sp.nvec, k.block, k.unroll, cus);
+    }
     const void *kern = shifted ? dot_shifted_table(xt, acc)
                        : !k.lane_form ? reduce_table(xt, op, acc, vb, k.unroll)
                        : xt == LIFT_F32 ? reduce_lanes_kernel_f32(op, vb, k.unroll, k.lane_form)
                                         : reduce_lanes_kernel_bf16(op, vb, k.unroll, k.lane_form);
     if (!kern)
         return LIFT_EUNSUPPORTED;
-    int cus = 0;
     st = cu_count(&cus);
     if (st != LIFT_OK)
         return st;
@@ -1550,14 +1578,20 @@ lift_status lift_scal_ex(int64_t n, float alpha, const float *x, float *out, con
     if (st != LIFT_OK)
         return st;
     Knobs k;
-    st = resolve(knobs, DEF_SCAL, 4, &k);
+    // Up to 16 MiB a vector of 16 bytes per thread where x and out share that
+    // alignment: the shortest chain of a load and a store, and the most
+    // work-groups (replayed from a graph, us, with 8 dwords per thread | this:
+    // 2^20 3.25 | 2.84, 3000001 7.2 | 5.4, 2^21 4.06 | 3.82, 2^22 6.85 | 6.86,
+    // 2^23 12.18 | 12.28).
+    Split3 sp;
+    const bool wide = !knobs && n <= 1 << 22 && n > 0 && split3(x, out, n, 4, 16, &sp);
+    st = resolve(knobs, wide ? Knobs{256, 16, 1, 1, 0, 32, 1, 1, 0} : DEF_SCAL, 4, &k);
     if (st != LIFT_OK)
         return st;
     if (k.vec_bytes < 4)
         return LIFT_EINVAL;
     if (n == 0)
         return LIFT_OK;
-    Split3 sp;
     int vb = k.vec_bytes;
     if (!split3(x, out, n, 4, vb, &sp)) {
         vb = 4;
