@@ -30,6 +30,8 @@ struct Entry {  // the C entry points, as addresses from the loaded library
     Status (*dot)(int64_t, int, const void *, const void *, int, int, void *, void *, size_t, const void *, void *);
     Status (*gemv)(int64_t, int64_t, float, int, const void *, int64_t, const float *, float, float *, int, const void *,
                    void *);
+    Status (*gemv_ws)(int64_t, int64_t, float, int, const void *, int64_t, const float *, float, float *, int, void *, size_t,
+                      const void *, void *);
     Status (*blackscholes)(int64_t, const float *, float, float, float, float, float *, const void *, void *);
     Status (*md)(int64_t, const float *, int64_t, const int32_t *, float, float, float, float *, const void *, void *);
 } entry;
@@ -37,6 +39,7 @@ struct Entry {  // the C entry points, as addresses from the loaded library
 PyObject *raw_stream = nullptr;      // device index -> stream handle of the current stream
 PyObject *make_workspace = nullptr;  // device -> the (device, stream) workspace tensor
 PyObject *check_status = nullptr;    // (status, name): raises
+PyObject *is_capturing = nullptr;    // whether the current stream is being captured
 
 // The tensor behind a plain torch.Tensor on a GPU, contiguous; else null.
 const at::Tensor *gpu_tensor(PyObject *o)
@@ -256,13 +259,28 @@ PyObject *call_gemv(PyObject *const *args)   // alpha, A, x, beta, y, acc
     if (code < 0 || A->dim() != 2 || !is_f32(*x) || !is_f32(*y))
         return none();
     const int64_t m = A->size(0), lda = A->size(1), cols = x->numel();
-    // few long rows take the workspace: the binding's own code
-    if (lda < cols || y->numel() != m || (cols * A->element_size() > 65536 && m <= 512))
+    if (lda < cols || y->numel() != m)
         return none();
     void *stream;
     if (!current_stream(*A, &stream))
         return nullptr;
+    // few long rows are split through the stream's workspace, but not under
+    // capture (as in the binding's own code)
+    at::Tensor ws;
+    if (cols * A->element_size() > 65536 && m <= 512) {
+        PyObject *capturing = PyObject_CallNoArgs(is_capturing);
+        if (!capturing)
+            return nullptr;
+        const int yes = PyObject_IsTrue(capturing);
+        Py_DECREF(capturing);
+        if (yes < 0 || (!yes && !workspace(args[1], *A, stream, &ws)))
+            return nullptr;
+    }
     const Status st = unlocked([&] {
+        if (ws.defined())
+            return entry.gemv_ws(m, cols, alpha, code, A->const_data_ptr(), lda, x->const_data_ptr<float>(), beta,
+                                 static_cast<float *>(y->data_ptr()), acc, ws.data_ptr(), (size_t)ws.numel(), nullptr,
+                                 stream);
         return entry.gemv(m, cols, alpha, code, A->const_data_ptr(), lda, x->const_data_ptr<float>(), beta,
                           static_cast<float *>(y->data_ptr()), acc, nullptr, stream);
     });
@@ -339,12 +357,13 @@ PyObject *guarded(PyObject *, PyObject *const *args, Py_ssize_t n)
     }
 }
 
-// init(addresses of scal_ex, asum_ex, dot_ex, gemv_ex, blackscholes_ex, md_ex, raw_stream, workspace, check)
+// init(addresses of scal_ex, asum_ex, dot_ex, gemv_ex, blackscholes_ex, md_ex, gemv_ex_ws, raw_stream, workspace, check,
+// is_capturing)
 PyObject *init(PyObject *, PyObject *args)
 {
-    unsigned long long a[6];
-    PyObject *s, *w, *c;
-    if (!PyArg_ParseTuple(args, "KKKKKKOOO", &a[0], &a[1], &a[2], &a[3], &a[4], &a[5], &s, &w, &c))
+    unsigned long long a[7];
+    PyObject *s, *w, *c, *g;
+    if (!PyArg_ParseTuple(args, "KKKKKKKOOOO", &a[0], &a[1], &a[2], &a[3], &a[4], &a[5], &a[6], &s, &w, &c, &g))
         return nullptr;
     entry.scal = reinterpret_cast<decltype(entry.scal)>(a[0]);
     entry.asum = reinterpret_cast<decltype(entry.asum)>(a[1]);
@@ -352,15 +371,19 @@ PyObject *init(PyObject *, PyObject *args)
     entry.gemv = reinterpret_cast<decltype(entry.gemv)>(a[3]);
     entry.blackscholes = reinterpret_cast<decltype(entry.blackscholes)>(a[4]);
     entry.md = reinterpret_cast<decltype(entry.md)>(a[5]);
+    entry.gemv_ws = reinterpret_cast<decltype(entry.gemv_ws)>(a[6]);
     Py_INCREF(s);
     Py_INCREF(w);
     Py_INCREF(c);
+    Py_INCREF(g);
     Py_XDECREF(raw_stream);
     Py_XDECREF(make_workspace);
     Py_XDECREF(check_status);
+    Py_XDECREF(is_capturing);
     raw_stream = s;
     make_workspace = w;
     check_status = c;
+    is_capturing = g;
     return none();
 }
 

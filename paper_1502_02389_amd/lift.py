@@ -170,9 +170,10 @@ def _native():
                 except ImportError:
                     native = _NoNative
                 else:
-                    names = ("scal", "asum", "dot", "gemv", "blackscholes", "md")
-                    at = [ctypes.cast(getattr(lib, f"lift_{n}_ex"), ctypes.c_void_p).value for n in names]
-                    native.init(*at, torch._C._cuda_getCurrentRawStream, workspace, _ok)
+                    names = ("scal_ex", "asum_ex", "dot_ex", "gemv_ex", "blackscholes_ex", "md_ex", "gemv_ex_ws")
+                    at = [ctypes.cast(getattr(lib, f"lift_{n}"), ctypes.c_void_p).value for n in names]
+                    native.init(*at, torch._C._cuda_getCurrentRawStream, workspace, _ok,
+                                torch.cuda.is_current_stream_capturing)
                 _NATIVE = native
     return _NATIVE
 

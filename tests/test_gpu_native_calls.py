@@ -99,3 +99,26 @@ def test_same_refusals(gpu_device, route):
         with pytest.raises(Exception) as e:
             call()
         assert isinstance(e.value, exc), (exc, e.value)
+
+
+@pytest.mark.parametrize("m, n", [(1, 32769), (8, 32768), (8, 32769), (22, 60184), (512, 33001), (513, 33001)])
+@pytest.mark.parametrize("captured", [False, True])
+def test_few_long_rows(gpu_device, m, n, captured):
+    """gemv on both sides of where rows are split through the stream's
+    workspace, on a stream of its own; under capture they are not."""
+    g = W.gen(97)
+    A, x, y = W.integers((m, n), -1, 1, g, "bf16"), W.integers(n, -1, 1, g), W.integers(m, -8, 8, g)
+    want = 2.0 * (A.double() @ x.double()) + 0.5 * y.double()
+    Ad, xd, yd, first = A.cuda(), x.cuda(), y.cuda(), y.cuda()
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        if captured:
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=s):
+                L.gemv(2.0, Ad, xd, 0.5, yd)
+        for _ in range(3):
+            yd.copy_(first)
+            graph.replay() if captured else L.gemv(2.0, Ad, xd, 0.5, yd)
+            s.synchronize()
+            assert torch.equal(yd.double().cpu(), want)
