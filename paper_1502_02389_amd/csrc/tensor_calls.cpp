@@ -265,7 +265,8 @@ PyObject *call_gemv(PyObject *const *args)   // alpha, A, x, beta, y, acc
     if (!current_stream(*A, &stream))
         return nullptr;
     // few long rows are split through the stream's workspace, but not under
-    // capture (as in the binding's own code)
+    // capture (as in the binding's own code, which takes 12 us whatever the
+    // size; through here, bf16: 8 x 33000 6.4, 22 x 60184 7.8, 8 x 65539 5.3 us)
     at::Tensor ws;
     if (cols * A->element_size() > 65536 && m <= 512) {
         PyObject *capturing = PyObject_CallNoArgs(is_capturing);
