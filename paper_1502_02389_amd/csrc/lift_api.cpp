@@ -764,10 +764,18 @@ lift_status gemv_by_rows(int64_t m, int64_t n, float alpha, int at, const void *
     }
     // Rows longer than that: panels of r rows, whole rows while there are
     // enough of them (3000 x 25137 fp32: r = 4 49.1, 2: 50.9, 1: 56.8 us),
-    // else cut in chunks (at least 32 KiB each) so that one or two
-    // work-groups per CU come out as nearly even as can be.
+    // else cut in chunks (at least 16 KiB each) so that one or two
+    // work-groups per CU come out as nearly even as can be.  Up to 32 KiB per
+    // CU the work-groups count, not the x they share: single rows (us, r = 2
+    // with chunks of 32 KiB | r = 1 with 16: 8 x 33000 bf16 6.5 | 4.4, 22 x
+    // 60184 bf16 6.6 | 4.6, 64 x 45000 bf16 8.0 | 5.4, 8 x 262144 fp32 6.0 | 5.2;
+    // but r = 2 | 1 with 16 KiB of 120 x 65539 bf16 7.2 | 7.4, 16 x 524288
+    // fp32 8.7 | 8.9).
     const int64_t per_class = (m + P - 1) / P;
-    const int r = per_class * P >= (int64_t)cus * 8 ? 4 : per_class > 1 && (ws || per_class * P > cus) ? 2 : 1;
+    const bool split = ws && per_class * P <= (int64_t)cus;
+    const int r = per_class * P >= (int64_t)cus * 8 ? 4
+                  : split && m * n * eb <= (int64_t)cus * 32768 ? 1
+                  : per_class > 1 && (ws || per_class * P > cus) ? 2 : 1;
     GemvPanelArgs p;
     p.rows = a;
     p.groups = P * ((per_class + r - 1) / r);
@@ -775,7 +783,7 @@ lift_status gemv_by_rows(int64_t m, int64_t n, float alpha, int at, const void *
     if (ws && p.groups <= cus) {
         int64_t one = cus / p.groups, two = 2 * cus / p.groups;
         int64_t c = two * p.groups * 100 > 2 * one * p.groups * 110 ? two : one;
-        c = std::min<int64_t>(c, std::max<int64_t>(1, n * eb / 32768));
+        c = std::min<int64_t>(c, std::max<int64_t>(1, n * eb / 16384));
         c = std::min<int64_t>(c, MAX_WORKGROUPS / (p.groups * r));
         p.chunks = std::max<int64_t>(1, c);
     }
