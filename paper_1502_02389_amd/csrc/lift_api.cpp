@@ -1774,8 +1774,7 @@ static lift_status md_passes(const MdArgs &args, int slices, int v, hipStream_t 
         s.md = a;
         s.lo = (uint32_t)(p * span);
         s.hi = (uint32_t)std::min<int64_t>(a.n, (p + 1) * span);
-        s.last = p == slices - 1;
-        if (s.last && t0)
+        if (p == slices - 1 && t0)
             g_time_stop = t1;
         st = launch(packed, grid, 256, &s, stream);
     }

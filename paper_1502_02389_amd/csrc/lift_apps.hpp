@@ -41,7 +41,6 @@ struct MdPackedArgs {
     MdArgs md;
     uint32_t lo;
     uint32_t hi;
-    int32_t last;   // the last pass: clears the marks
 };
 
 const void *md_sort_kernel_table(int v);

@@ -308,3 +308,25 @@ def test_passes_in_a_graph_and_under_the_timing_hook(gpu_device):
             s.synchronize()
             assert torch.equal(out, want)
     graph.reset()
+
+
+@pytest.mark.parametrize("n,k,order", [(469_001, 140, "random"), (800_003, 21, "random"), (470_000, 64, "mixed")])
+def test_passes_with_padding_anywhere(gpu_device, n, k, order):
+    """Rows whose padding comes first, rows with holes, empty rows, rows of one
+    slice only (sorted either way): every pass reads what it still needs."""
+    pos, nbr = _large_system(n, k, order, n % 1000, DEV)
+    i = torch.arange(n, device=DEV)[:, None]
+    hole = (torch.arange(k, device=DEV)[None, :] * 7 + i) % 5 == 0
+    nbr = torch.where((i // 8 % 6 == 1) & hole, -1, nbr)
+    nbr = torch.where(i // 8 % 6 == 2, nbr.flip(1), nbr)
+    nbr = torch.where(i // 4 % 12 == 6, -1, nbr)
+    nbr = torch.where(i // 8 % 6 == 4, nbr.sort(1).values, nbr)
+    nbr = torch.where(i // 8 % 6 == 5, nbr.sort(1, descending=True).values, nbr).contiguous()
+    params = (W.MD_CUTOFF, W.MD_EPSILON, W.MD_SIGMA)
+    banner("md passes padding", n, k, order)
+    out = torch.full((n, 4), float("nan"), device=DEV)
+    L.md(pos, nbr, *params, out=out)
+    first = out.clone()
+    L.md(pos, nbr, *params, out=out)
+    assert torch.equal(first.view(torch.int32), out.view(torch.int32))
+    check(out, pos.cpu(), nbr.cpu(), params)
