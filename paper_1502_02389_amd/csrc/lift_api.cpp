@@ -1137,20 +1137,50 @@ lift_status batch_plan_waves(const lift_problem *probs, int32_t count, int stora
     const double total = batch_reads(probs, count, eb, &filled);
     const int64_t tile = (int64_t)std::max(8192.0, total / std::max<int64_t>(waves / 2, waves - filled));
 
-    struct Planned {
+    // Equal tiles of one problem, one after the other: a, b and out advance by
+    // these many bytes, a reduction's slot and its number in its problem by 1.
+    struct Run {
         WaveTile t;
-        int64_t cost;
+        int64_t count, cost, da, db, dout;
     };
-    std::vector<Planned> tiles;
+    std::vector<Run> runs;
+    runs.reserve(2 * (size_t)count);
     int64_t slots = 0, kinds[2] = {0, 0};
+    // `total` units in tiles of `unit`: a run of whole ones and the rest
+    const auto cut = [&](Run r, int64_t total_units, int64_t unit, int32_t WaveTile::*length, int64_t unit_bytes) {
+        const int64_t whole = total_units / unit, rest = total_units - whole * unit;
+        for (int last = 0; last < 2; ++last) {
+            Run part = r;
+            part.count = last ? rest > 0 || total_units == 0 : whole;
+            if (part.count == 0)
+                continue;
+            part.t.*length = (int32_t)(last ? rest : unit);
+            part.cost = (last ? rest : unit) * unit_bytes + 4096;
+            if (last) {
+                const auto advance = [&](const void *p, int64_t d) {
+                    return p ? static_cast<const char *>(p) + whole * d : nullptr;
+                };
+                part.t.a = advance(r.t.a, r.da);
+                part.t.b = advance(r.t.b, r.db);
+                part.t.out = static_cast<char *>(r.t.out) + whole * r.dout;
+                if (r.t.kind != LIFT_KIND_GEMV) {
+                    part.t.rows += (int32_t)whole;
+                    part.t.slot += (int32_t)whole;
+                }
+            }
+            kinds[r.t.kind == LIFT_KIND_GEMV] += part.count;
+            runs.push_back(part);
+        }
+    };
     for (int32_t i = 0; i < count; ++i) {
         const lift_problem &q = probs[i];
-        Planned p;
-        std::memset(&p, 0, sizeof p);
-        p.t.kind = q.kind;
-        p.t.problem = i;
-        p.t.alpha = q.alpha;
-        p.t.beta = q.beta;
+        Run r;
+        std::memset(&r, 0, sizeof r);
+        r.t.kind = q.kind;
+        r.t.problem = i;
+        r.t.alpha = q.alpha;
+        r.t.beta = q.beta;
+        r.t.out = q.out;
         if (q.kind == LIFT_KIND_GEMV) {
             if (q.m == 0)
                 continue;
@@ -1167,18 +1197,14 @@ lift_status batch_plan_waves(const lift_problem *probs, int32_t count, int stora
             const int64_t nt = (q.m + want - 1) / want;
             int64_t rows = (q.m + nt - 1) / nt;
             rows = std::min<int64_t>((rows + unit - 1) / unit * unit, 1 << 30);
-            for (int64_t r = 0; r < q.m; r += rows) {
-                p.t.a = static_cast<const char *>(q.a) + r * q.lda * eb;
-                p.t.b = q.b;
-                p.t.out = static_cast<float *>(q.out) + r;
-                p.t.pitch = q.lda * eb;
-                p.t.n = (int32_t)q.n;
-                p.t.rows = (int32_t)std::min(rows, q.m - r);
-                p.t.ntiles = 1;
-                p.cost = p.t.rows * q.n * eb + 4096;
-                tiles.push_back(p);
-                ++kinds[1];
-            }
+            r.t.a = q.a;
+            r.t.b = q.b;
+            r.t.pitch = q.lda * eb;
+            r.t.n = (int32_t)q.n;
+            r.t.ntiles = 1;
+            r.da = rows * q.lda * eb;
+            r.dout = rows * 4;
+            cut(r, q.m, rows, &WaveTile::rows, q.n * eb);
         } else {
             const int64_t streams = q.kind == LIFT_KIND_DOT ? 2 : 1;
             const int64_t want = std::max<int64_t>(64 * e, tile / (eb * streams));
@@ -1188,57 +1214,58 @@ lift_status batch_plan_waves(const lift_problem *probs, int32_t count, int stora
             nt = std::max<int64_t>(1, (q.n + len - 1) / len);
             if (slots + nt > INT32_MAX)
                 return LIFT_EUNSUPPORTED;
-            for (int64_t k = 0; k < nt; ++k) {
-                const int64_t at = k * len;
-                p.t.a = q.n ? static_cast<const char *>(q.a) + at * eb : nullptr;
-                p.t.b = q.n && streams == 2 ? static_cast<const char *>(q.b) + at * eb : nullptr;
-                p.t.out = q.out;
-                p.t.n = (int32_t)std::min(len, q.n - at);
-                p.t.rows = (int32_t)k;
-                p.t.ntiles = (int32_t)nt;
-                p.t.slot = (int32_t)(slots + k);
-                p.cost = p.t.n * eb * streams + 4096;
-                tiles.push_back(p);
-                ++kinds[0];
-            }
+            r.t.a = q.n ? q.a : nullptr;
+            r.t.b = q.n && streams == 2 ? q.b : nullptr;
+            r.t.ntiles = (int32_t)nt;
+            r.t.slot = (int32_t)slots;
+            r.da = r.db = len * eb;
+            cut(r, q.n, len, &WaveTile::n, eb * streams);
             slots += nt;
         }
     }
-    if ((int64_t)tiles.size() >= 1 << 30)
+    const int64_t ntiles = kinds[0] + kinds[1];
+    if (ntiles >= 1 << 30)
         return LIFT_EUNSUPPORTED;
-    std::stable_sort(tiles.begin(), tiles.end(), [](const Planned &x, const Planned &y) { return x.cost > y.cost; });
-    const int64_t ntiles = (int64_t)tiles.size();
+    std::stable_sort(runs.begin(), runs.end(), [](const Run &x, const Run &y) { return x.cost > y.cost; });
     const int64_t grid = std::min<int64_t>(most, (std::max<int64_t>(ntiles, 1) + DRAW_LISTS - 1) / DRAW_LISTS * DRAW_LISTS);
-    std::vector<WaveTile> table((size_t)ntiles);
-    std::vector<int32_t> records((size_t)ntiles);   // stamps: the reductions' tiles first, then gemv's
-    int64_t at[2] = {0, kinds[0]};
-    for (int64_t i = 0; i < ntiles; ++i) {
-        table[(size_t)i] = tiles[(size_t)i].t;
-        records[(size_t)i] = (int32_t)at[table[(size_t)i].kind == LIFT_KIND_GEMV]++;
-    }
 
     int dev = 0;
     hipError_t he = hipGetDevice(&dev);
     if (he != hipSuccess)
         return hip_fail(he);
     // one allocation: draw counters | counter and groups of work-groups that
-    // left | per-problem counters | tiles | records | slots
+    // left | per-problem counters | tiles | records | slots; all but the slots
+    // in one upload
     auto up = [](int64_t v) { return (v + 255) / 256 * 256; };
     const int64_t off_done = up(DRAW_LISTS * WS_GROUP_STRIDE), off_groups = off_done + 256;
     const int64_t off_pc = off_groups + up((grid + ARRIVAL_GROUP - 1) / ARRIVAL_GROUP * WS_GROUP_STRIDE);
     const int64_t off_ti = off_pc + up(std::max<int64_t>(count, 1) * 4);
     const int64_t off_re = off_ti + up(std::max<int64_t>(ntiles, 1) * (int64_t)sizeof(WaveTile));
     const int64_t off_sl = off_re + up(std::max<int64_t>(ntiles, 1) * 4);
+    std::vector<char> image((size_t)off_sl);
+    WaveTile *table = reinterpret_cast<WaveTile *>(image.data() + off_ti);
+    int32_t *records = reinterpret_cast<int32_t *>(image.data() + off_re);   // stamps: reductions first, then gemv
+    int64_t at[2] = {0, kinds[0]};
+    for (const Run &r : runs) {
+        WaveTile w = r.t;
+        for (int64_t k = 0; k < r.count; ++k) {
+            *table++ = w;
+            *records++ = (int32_t)at[w.kind == LIFT_KIND_GEMV]++;
+            w.a = w.a ? static_cast<const char *>(w.a) + r.da : nullptr;
+            w.b = w.b ? static_cast<const char *>(w.b) + r.db : nullptr;
+            w.out = static_cast<char *>(w.out) + r.dout;
+            if (w.kind != LIFT_KIND_GEMV) {
+                ++w.rows;
+                ++w.slot;
+            }
+        }
+    }
     void *mem = nullptr;
     he = hipMalloc(&mem, (size_t)(off_sl + std::max<int64_t>(slots, 1) * WS_SLOT));
     if (he != hipSuccess)
         return hip_fail(he);
     char *base = static_cast<char *>(mem);
-    if ((he = hipMemset(base, 0, (size_t)off_ti)) != hipSuccess ||
-        (ntiles > 0 && ((he = hipMemcpy(base + off_ti, table.data(), table.size() * sizeof(WaveTile),
-                                        hipMemcpyHostToDevice)) != hipSuccess ||
-                        (he = hipMemcpy(base + off_re, records.data(), records.size() * 4, hipMemcpyHostToDevice)) !=
-                            hipSuccess))) {
+    if ((he = hipMemcpy(base, image.data(), image.size(), hipMemcpyHostToDevice)) != hipSuccess) {
         hipFree(mem);
         return hip_fail(he);
     }
