@@ -156,7 +156,8 @@ typedef enum lift_lane_form {
  *      cache, used only on a device of the architecture and compute-unit
  *      count it was tuned on;
  *   3. else the library defaults (gemv: also where the tuned knobs' vector
- *      loads do not fit A's row starts and x's alignment; its launch then
+ *      loads do not fit A's row starts and x's alignment, or a row takes more
+ *      steps of them than the power of two they were tuned on; its launch then
  *      goes by row length, for any alignment, as it does for all-zero knobs;
  *      dot: also where x and y lie in different 16-byte phases, whose launch
  *      without knobs then reads both in vectors).

@@ -840,8 +840,17 @@ lift_status gemv_common(int64_t m, int64_t n, float alpha, int at, const void *A
     const int64_t xalign = std::min<int64_t>(e * 4, 16);
     const bool vec = n > 0 && aligned(A, vb) && (lda * eb) % vb == 0 && aligned(x, xalign);
     // The launch is the library's choice: without knobs, unless a tuned entry
-    // (found on aligned rows) or the environment override decides it.
-    const bool choose = given ? all_zero(given) : !forced_config().present && (!knobs || !vec);
+    // (found on aligned rows of a power of two) or the environment override
+    // decides it.  An entry stands for rows that take as many of its steps as
+    // that power of two; one more step, mostly empty, or x no longer in
+    // registers costs more than the row-length form (us, tuned | by rows: 9000 x
+    // 30000 bf16 128 | 87, 12000 x 12000 fp32 91.3 | 85.7, 10000 x 20000 fp32 121
+    // | 114, 5000 x 4104 fp32 15.7 | 14.3; but 4096 x 4096 fp32 11.5 | 12.1,
+    // 8192 x 16384 fp32 76.0 | 77.6).
+    const int64_t row_step = (int64_t)(k.row_split == 2 ? k.block : 64) * k.unroll * e;
+    const auto steps = [&](int64_t columns) { return (columns + row_step - 1) / row_step; };
+    const bool as_tuned = vec && steps(n) == steps((int64_t)1 << log2_bucket(n));
+    const bool choose = given ? all_zero(given) : !forced_config().present && (!knobs || !as_tuned);
     if (choose && n > 0)
         return gemv_by_rows(m, n, alpha, at, A, lda, x, beta, y, acc, static_cast<char *>(ws), stream);
     if (!vec) {

@@ -121,3 +121,21 @@ def test_ws_entry_rejects_bad_workspace(gpu_device):
     assert L.lift_gemv_ex_ws(*args, 0, ws.numel(), None, s) == L.LIFT_EWORKSPACE
     assert L.lift_gemv_ex_ws(*args, ws.data_ptr(), ws.numel() - 1, None, s) == L.LIFT_EWORKSPACE
     assert L.lift_gemv_ex_ws(*args, ws.data_ptr() + 4, ws.numel(), None, s) == L.LIFT_EINVAL
+
+
+@pytest.mark.parametrize("m, n, storage", [(4096, 4096, "f32"), (4090, 4100, "f32"), (2100, 8188, "f32"), (8200, 8192, "f32"),
+                                           (7000, 9600, "f32"), (16385, 16384, "bf16"), (16000, 16392, "bf16"),
+                                           (9000, 30000, "f16")])
+def test_both_sides_of_the_tuned_rows(gpu_device, m, n, storage):
+    """Aligned rows of a power of two (a tuned entry's) and just off it, in the
+    size buckets that have tuned entries: exact on small integers."""
+    g = torch.Generator(DEV)
+    g.manual_seed(m + n)
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[storage]
+    A = torch.randint(-1, 2, (m, n), generator=g, device=DEV, dtype=torch.int8).to(dt)
+    x = torch.randint(-3, 4, (n,), generator=g, device=DEV).float()
+    y = torch.randint(-8, 9, (m,), generator=g, device=DEV).float()
+    want = torch.cat([2.0 * (a.double() @ x.double()) for a in A.split(2048)]) + 0.5 * y.double()
+    banner("tuned rows", m, n, storage)
+    L.gemv(2.0, A, x, 0.5, y)
+    assert torch.equal(y.double(), want)
