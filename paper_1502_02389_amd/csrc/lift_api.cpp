@@ -743,7 +743,13 @@ lift_status gemv_by_rows(int64_t m, int64_t n, float alpha, int at, const void *
         // fp32); rows of 32 KiB and more do better as more, shorter-lived
         // work-groups (16384 x 8191 fp32: 16 per CU 80.3, 2 per CU 82.8 us)
         // of at least 4 rows, each reading its part of x once (3000 x 25137
-        // bf16: one row each 35.6, 2 work-groups per CU 27.9 us).
+        // bf16: one row each 35.6, 2 work-groups per CU 27.9 us) -- but not
+        // between 32 and 56 KiB, where a work-group has 5 or 6 wavefronts, no
+        // multiple of a CU's 4 SIMDs: 2 per CU, 3 from 48 KiB on (us, as the
+        // others | this: 14000 x 9800 fp32 89.3 | 86.2, 13000 x 8400 fp32 70.0 |
+        // 67.4, 13000 x 20000 bf16 84.7 | 82.2, 7900 x 12000 fp32 57.4 | 56.4,
+        // 12000 x 24000 bf16 88.6 | 85.6; 8500 x 16000 fp32, 64 KiB, 16 per CU
+        // 77.6, 2 per CU 80.1).
         int waves = 8, v = 8;
         const int64_t need = (vecs + 63) / 64;
         for (int w = 8; w >= 3; --w)
@@ -756,7 +762,9 @@ lift_status gemv_by_rows(int64_t m, int64_t n, float alpha, int at, const void *
         if (!kern)
             return LIFT_EUNSUPPORTED;
         const int64_t bytes = (int64_t)waves * v * 1024;
-        const int64_t per_cu = std::max<int64_t>(2, bytes >= 32768 ? std::min<int64_t>(16, m / (4 * (int64_t)cus)) : 40960 / bytes);
+        const int64_t per_cu = bytes > 32768 && bytes < 57344 ? (bytes < 49152 ? 2 : 3)
+                               : bytes >= 32768 ? std::max<int64_t>(2, std::min<int64_t>(16, m / (4 * (int64_t)cus)))
+                                                : std::max<int64_t>(2, 40960 / bytes);
         int64_t grid = std::min<int64_t>(m, (int64_t)cus * per_cu);
         if (P == 2)
             grid -= grid % 2;
