@@ -33,10 +33,14 @@
  * Results.    A reduction writes its scalar to DEVICE memory (`result`): the
  *             paper's reduce returns a one-element array, T[] -> T[1].
  * Workspace.  asum and dot take a device workspace `ws` of `ws_bytes` bytes,
- *             at least lift_workspace_bytes().  It must be zero-filled ONCE
- *             before its first use; every call leaves the counters and arrival
- *             marks it uses zeroed again, so replays need no memset.  Calls that may run concurrently (different streams)
- *             need different workspaces.
+ *             at least lift_workspace_bytes().  All of it must be zero-filled
+ *             ONCE before its first use; every call leaves what it uses of it
+ *             zeroed again, so replays need no memset.  Calls that may run
+ *             concurrently (different streams, or graphs that may be replayed
+ *             next to each other or to such calls) need different workspaces:
+ *             two that share one run to their end, but may get wrong results
+ *             and leave the workspace unfit for further calls until it is
+ *             zero-filled again.
  * Errors.     Arguments are checked before any HIP call.  LIFT_EINVAL: bad
  *             size, null pointer with a non-empty extent, pointer not aligned
  *             to its element size, partial overlap of an output with an
@@ -54,11 +58,14 @@
  *             partial sums stay below 2^24 in magnitude give identical
  *             results under every knob set.  The cross-work-group combine
  *             relies on gfx950's memory behaviour rather than on fences:
- *             partials are written with agent-scope atomic stores (which the
- *             hardware writes through past the XCD-private L2) of one word
- *             that shows its arrival by itself, and the combining work-group,
- *             the last of the grid, reads them with agent-scope atomic loads
- *             (which miss the L2) until all are there.  Built and tested for
+ *             partials are written with agent-scope atomics (which the
+ *             hardware performs past the XCD-private L2) as one word that
+ *             shows its arrival by itself, and the last work-group of the grid
+ *             reads them with agent-scope atomic loads (which miss the L2)
+ *             until all are there.  It looks for them a bounded number of
+ *             times; after that the work-group whose partial comes last
+ *             combines, in the same order, so a launch never depends on which
+ *             of its work-groups run at the same time.  Built and tested for
  *             gfx950 only.
  */
 #ifndef LIFT_H
@@ -466,12 +473,12 @@ lift_status lift_time_next_launch(hipEvent_t start, hipEvent_t stop);
  * kernel, identical in arithmetic, which writes 8 words per work-group into
  * `stamps` (device memory owned by the caller, `capacity` work-groups):
  * readings of the device's constant wall clock at entry, when its streaming
- * loop is done, after its work-group tree, once its partial is stored, once
- * its arrival is counted, and at its end (the combining work-group: after
- * the combine), then ids (bit 32: the work-group that combined; bits 16-19:
+ * loop is done, after its work-group tree, when its partial leaves for the
+ * combine (in two words), and at its end (the combining work-group: after
+ * the combine; the others: the same reading again), then ids (bit 32: the work-group that combined; bits 16-19:
  * its XCC; bits 0-7: HW_ID[15:8], CU / shader array / shader engine), then
  * one unused word (a launch of one work-group, which writes the result
- * itself, takes the store, arrival and end readings together).  If the next call is lift_batch_run instead (binary32
+ * itself, takes the last three readings together).  If the next call is lift_batch_run instead (binary32
  * accumulation, F32 or BF16 storage), both of its launches run the stamped
  * instances of their kernels, which write 4 words per tile (`capacity`
  * counts tiles): the reduction tiles in the order of that launch's tile
@@ -486,6 +493,13 @@ lift_status lift_time_next_launch(hipEvent_t start, hipEvent_t stop);
  * either way).  stamps == NULL disarms it.
  * LIFT_EINVAL: capacity <= 0, stamps not 8-byte aligned or clock_khz NULL. */
 lift_status lift_stamp_next_launch(uint64_t *stamps, int64_t capacity, int32_t *clock_khz);
+
+/* Diagnostic: how often the next launch on this thread of an asum, a dot or a
+ * gemv with split rows looks for partials that have not come before it hands
+ * its combine over (see Determinism above); 0: once, then it hands over at once
+ * if any is missing.  One-shot; results do not depend on it.  LIFT_EINVAL:
+ * rounds < 0. */
+lift_status lift_combine_rounds_next_launch(int32_t rounds);
 
 /* The knobs a call with knobs == NULL would run with on a device of
  * architecture `arch` (e.g. "gfx950"; NULL = the current device, a HIP

@@ -33,6 +33,9 @@ thread_local hipEvent_t g_time_start = nullptr;  // armed by lift_time_next_laun
 thread_local hipEvent_t g_time_stop = nullptr;
 thread_local uint64_t *g_stamps = nullptr;       // armed by lift_stamp_next_launch
 thread_local int64_t g_stamp_capacity = 0;
+thread_local int32_t g_rounds = COMBINE_ROUNDS;  // set by lift_combine_rounds_next_launch
+
+int32_t take_rounds() { return std::exchange(g_rounds, COMBINE_ROUNDS); }
 
 constexpr int MAX_DEVICES = 64;
 std::atomic<int> g_cu_count[MAX_DEVICES];
@@ -646,6 +649,7 @@ lift_status reduce_common(int op, int64_t n, int xt, const void *x, const void *
     a.result = result;
     a.result_f64 = rt == LIFT_F64;
     a.interleave = k.interleave;
+    a.rounds = take_rounds();
     a.stamps = nullptr;
     if (g_stamps) {  // the stamped instance of the same kernel (one-shot)
         uint64_t *buf = g_stamps;
@@ -799,6 +803,7 @@ lift_status gemv_by_rows(int64_t m, int64_t n, float alpha, int at, const void *
     p.chunk = (nv + p.chunks - 1) / p.chunks;
     p.chunks = std::max<int64_t>(1, (nv + p.chunk - 1) / p.chunk);
     p.ws = ws;
+    p.rounds = take_rounds();
     const void *kern = gemv_panel_table(at, acc, r);
     if (!kern)
         return LIFT_EUNSUPPORTED;
@@ -2154,6 +2159,14 @@ lift_status lift_stamp_next_launch(uint64_t *stamps, int64_t capacity, int32_t *
     *clock_khz = khz;
     g_stamps = stamps;
     g_stamp_capacity = capacity;
+    return LIFT_OK;
+}
+
+lift_status lift_combine_rounds_next_launch(int32_t rounds)
+{
+    if (rounds < 0)
+        return LIFT_EINVAL;
+    g_rounds = rounds;
     return LIFT_OK;
 }
 

@@ -291,8 +291,8 @@ __global__ void __launch_bounds__(512) gemv_rows_wg_kernel(GemvRowsArgs a)
 // b % groups and chunk b / groups, so the work-groups that run together share
 // their part of x in the cache.  The R rows of a group start alike (they are
 // `classes` apart) and share every x load.  One chunk: the rows are finished
-// here.  More: the partials go to the group's slots of the workspace and the
-// work-group that arrives last folds them in chunk order (lane t: chunks t,
+// here.  More: the group's work-groups meet in its slots of the workspace
+// (meet()) and one of them folds the partials in chunk order (lane t: chunks t,
 // t + 64, ..., then the wave butterfly), so the result does not depend on the
 // order of arrival.
 template <class T, int ACC, int R, int U>
@@ -413,39 +413,19 @@ __global__ void __launch_bounds__(512) gemv_panel_kernel(GemvPanelArgs a)
             a.rows.y[r0 + t * P] = row_epilogue<ACC>(d, a.rows.alpha, a.rows.beta, yold);
         return;
     }
-    const int64_t slot0 = group * a.chunks * R;   // [row][chunk]
-    if (t < R)
-        store_word(slot_word(a.ws, slot0 + t * a.chunks + chunk), to_word(d));
-    unsigned *counter = reinterpret_cast<unsigned *>(a.ws + WS_GROUPS + group * WS_GROUP_STRIDE);
-    int last = 0;
-    if (t == 0)
-        last = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-               (unsigned)(a.chunks - 1);
-    if (!__builtin_amdgcn_readfirstlane(last))
+    D v[R];
+    unsigned *pending = reinterpret_cast<unsigned *>(a.ws + WS_GROUPS + group * WS_GROUP_STRIDE);
+    if (!meet<1>(a.ws, pending, group * a.chunks * R, a.chunks, chunk, d, a.rounds, v))
         return;
     D sum = zero_of<D>();
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-        D s = zero_of<D>();
-        for (int64_t c = t; c < a.chunks; c += 64) {
-            // every chunk's store was issued before its arrival was counted:
-            // at most its way to memory is left to wait for
-            uint64_t *slot = slot_word(a.ws, slot0 + i * a.chunks + c);
-            uint64_t w;
-            do {
-                w = load_word(slot);
-            } while (!word_arrived<D>(w));
-            store_word(slot, 0);
-            s = merge(s, from_word<D>(w));
-        }
-        s = lanes_sum<64>(s);
+        const D s = lanes_sum<64>(v[i]);
         if (t == i)
             sum = s;
     }
     if (row_lane)
         a.rows.y[r0 + t * P] = row_epilogue<ACC>(sum, a.rows.alpha, a.rows.beta, yold);
-    if (t == 0)
-        __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Instances.  rows: (L, V) covering the row, R rows per group in flight.

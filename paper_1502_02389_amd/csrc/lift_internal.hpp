@@ -11,18 +11,30 @@ enum Dtype { DT_F32 = 0, DT_BF16 = 1, DT_F16 = 2, DT_F64 = 3 };
 enum Op { OP_ASUM = 0, OP_DOT = 1 };
 enum Acc { ACC_F32 = 0, ACC_COMP = 1, ACC_F64 = 2 };
 
-// Workspace layout: the global arrival counter in the first 256 bytes; one
-// group arrival counter per ARRIVAL_GROUP work-groups, each in its own
-// 64-byte line; then one 16-byte partial slot per work-group.  Arrivals are
-// counted in two levels because agent-scope atomics on a single address
+// Workspace layout: the global arrival counter and the count of marked slots
+// in the first 256 bytes; one group counter per ARRIVAL_GROUP work-groups, each
+// in its own 64-byte line; then one 16-byte partial slot per work-group.  All
+// of it is zero before its first use, and all that a call uses afterwards.
+//
+// A slot's second word is a partial of the default reductions and of split
+// gemv rows, whose arrival the word itself shows: it has to be clear when a
+// call begins, and the call clears what it used.  The first word is an untagged
+// partial of the small lane forms (those stay), which count arrivals: in two
+// levels (ARRIVAL_GROUP), because agent-scope atomics on a single address
 // serialize (about 10 ns each on MI355X) when every work-group finishes at
-// once.
+// once.  A split gemv's row group g counts its marked slots in group counter g.
 constexpr int32_t MAX_WORKGROUPS = 8192;
 constexpr int32_t ARRIVAL_GROUP = 16;
+constexpr int64_t WS_PENDING = 64;                      // offset of the count of marked slots
 constexpr int64_t WS_GROUPS = 256;                      // offset of the group counters
 constexpr int64_t WS_GROUP_STRIDE = 64;
 constexpr int64_t WS_HEADER = WS_GROUPS + (MAX_WORKGROUPS / ARRIVAL_GROUP) * WS_GROUP_STRIDE;
 constexpr int64_t WS_SLOT = 16;
+
+// How often the last work-group looks for the others' partials before it hands
+// the combine over (meet()).  A look takes a device-scope round trip, about a
+// microsecond; the last work-group is rarely more than some tens ahead.
+constexpr int32_t COMBINE_ROUNDS = 4096;
 
 // reduce(add, 0) . map(abs) over x, or reduce(add, 0) . map(mult) . zip(x, y).
 // Elements [0, head) are scalars before the first VB-aligned address; then
@@ -39,14 +51,15 @@ struct ReduceArgs {
     void *result;
     int32_t result_f64;
     int32_t interleave;  // 1: work-group b takes steps b, b + G, ... (grid-stride)
+    int32_t rounds;      // looks for missing partials (COMBINE_ROUNDS)
     uint64_t *stamps;    // stamped instances only: STAMPS_PER_WG clock readings per work-group
 };
 
 // Clock readings of a stamped reduction launch, per work-group (the device's
 // constant wall clock): [0] entry, [1] streaming loop done, [2] work-group
-// tree done, [3] partial stored, [4] arrival counted, [5] end (the last
-// work-group: after the combine; the others: = [4]); [6] ids: bit 32 set in
-// the work-group that combined, bits 16-19 its XCC, bits 0-7 HW_ID[15:8]
+// tree done, [3] = [4] its partial is about to leave, [5] end (the work-group
+// that combines: after the combine; the others: = [4]); [6] ids: bit 32 set
+// in the work-group that combined, bits 16-19 its XCC, bits 0-7 HW_ID[15:8]
 // (CU, shader array, shader engine); [7] unused.
 constexpr int STAMPS_PER_WG = 8;
 const void *reduce_kernel_stamped_f32(int op, int unroll);
@@ -110,13 +123,14 @@ struct GemvRowsArgs {
 
 // ... with the rows in `groups` groups of R and the columns in `chunks`
 // chunks of `chunk` vectors; ws: group counters and slots of the reduction
-// workspace (unused with one chunk).
+// workspace (unused with one chunk); rounds as in ReduceArgs.
 struct GemvPanelArgs {
     GemvRowsArgs rows;
     int64_t groups;
     int64_t chunks;
     int64_t chunk;
     char *ws;
+    int32_t rounds;
 };
 
 // ---- batched form ----------------------------------------------------------

@@ -15,15 +15,16 @@
 // its partial with a tag that shows its arrival, and one wavefront of the
 // grid's last work-group folds all partials (lane t: partials t, t + 64, ...;
 // then the wave butterfly) as they arrive, writes the result and clears the
-// tags for the next call.  No float atomics, so the result is deterministic;
-// only the work-group dispatched last ever waits, and only for work-groups
-// that do not, so the grid always drains.
+// tags for the next call.  No float atomics, so the result is deterministic.
+// The last work-group's wait is bounded: past it the work-group whose partial
+// is the last to come folds instead (meet()), so the grid drains in whatever
+// order its work-groups run.
 //
 // Cross-XCD visibility without cache maintenance: the partials are written
-// and read with agent-scope atomic stores / loads, which gfx950 performs
-// device-coherently (write-through / miss in the per-XCD L2), value and tag in
-// one word.  An agent-scope release/acquire fence would instead write back and
-// invalidate the whole L2 of the XCD in every work-group.
+// and read with agent-scope atomics, which gfx950 performs device-coherently
+// (past the per-XCD L2), value and tag in one word.  An agent-scope
+// release/acquire fence would instead write back and invalidate the whole L2
+// of the XCD in every work-group.
 #pragma once
 
 #include "lift_device.hpp"
@@ -199,7 +200,7 @@ __device__ __forceinline__ Pair load_coherent<Pair>(const char *p)
 }
 
 // Partials whose arrival shows in the slot itself: one 64-bit word per
-// partial, written by one store, so a reader sees all of it or none and needs
+// partial, written at once, so a reader sees all of it or none and needs
 // no counter and no ordering between stores.  A word of zeros (the workspace
 // before its first use, and again once the reader has cleared what it took)
 // or of ones has not arrived:
@@ -214,6 +215,9 @@ __device__ __forceinline__ Pair load_coherent<Pair>(const char *p)
 constexpr uint32_t SLOT_TAG = 0x4c494654u;
 constexpr uint64_t SLOT_PAIR = 0x805ffffe7fa5c3e1ull;   // error half above, sum half below
 constexpr uint64_t SLOT_F64 = 0x7ff4c3e15a96f00dull;
+// Left in the slot of a partial that has not arrived by a reader that waits no
+// longer (meet()): no partial's word, by the same reasons.
+constexpr uint64_t SLOT_MARK = 1;
 
 __device__ __forceinline__ uint64_t to_word(float v)
 {
@@ -227,7 +231,7 @@ __device__ __forceinline__ bool word_arrived(uint64_t w)
     if constexpr (sizeof(S) == 4)
         return (uint32_t)(w >> 32) == SLOT_TAG;
     else
-        return w + 1 > 1;   // neither 0 nor ~0
+        return w + 1 > 2;   // not 0, ~0 or SLOT_MARK
 }
 template <class S>
 __device__ __forceinline__ S from_word(uint64_t w);
@@ -275,13 +279,13 @@ __device__ __forceinline__ bool arrive(unsigned *global, char *group_base)
     return prev == groups - 1;
 }
 
-// Lane 0's value, for the whole wave.
-__device__ __forceinline__ float first_lane(float v) { return readlane(v, 0); }
-__device__ __forceinline__ Pair first_lane(Pair v) { return {readlane(v.s, 0), readlane(v.c, 0)}; }
-__device__ __forceinline__ double first_lane(double v)
+// Lane i's value, for the whole wave.
+__device__ __forceinline__ float lane_value(float v, int i) { return readlane(v, i); }
+__device__ __forceinline__ Pair lane_value(Pair v, int i) { return {readlane(v.s, i), readlane(v.c, i)}; }
+__device__ __forceinline__ double lane_value(double v, int i)
 {
     const uint64_t w = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)w), hi = __builtin_amdgcn_readfirstlane((uint32_t)(w >> 32));
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)w, i), hi = __builtin_amdgcn_readlane((uint32_t)(w >> 32), i);
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
@@ -356,49 +360,171 @@ __device__ __forceinline__ void stamp_arrival(const ReduceArgs &a, int last)
 }
 
 // Lane t of a wavefront folds partials t, t + 64, ... of [0, last) and
-// `own`, partial `last`, into v in that order, each as soon as it is there,
-// and clears the slots.  LOADS loads in flight, all issued again while one of
-// them is missing.
-template <class ST, int LOADS>
-__device__ __forceinline__ void fold_slots(char *ws, int64_t last, ST own, ST &v)
+// `own`, partial `last`, into v in that order, each as soon as it is there.
+// LOADS loads in flight, all issued again while one of them is missing, `rounds`
+// times in all: it ends negative if one still is (v is then of no use).  CLEAR:
+// the last LOADS x 64 slots are cleared on the way, all of their partials having
+// come (after the fold this takes 0.1 us of every reduction).
+template <class ST, int LOADS, bool CLEAR>
+__device__ __forceinline__ void fold_slots(char *ws, int64_t slot0, int64_t last, ST own, int &rounds, ST &v)
 {
     const int t = threadIdx.x & 63;
     for (int64_t base = 0; base <= last; base += 64 * LOADS) {
         uint64_t w[LOADS];
         bool waits;
         do {
-#pragma unroll
-            for (int k = 0; k < LOADS; ++k)
-                w[k] = load_word(slot_word(ws, min(base + t + 64 * k, last - 1)));
             waits = false;
+            if constexpr (LOADS == 1) {
+                w[0] = base + t < last ? load_word(slot_word(ws, slot0 + base + t)) : 0;
+                waits = base + t < last && !word_arrived<ST>(w[0]);
+            } else {
 #pragma unroll
-            for (int k = 0; k < LOADS; ++k)
-                waits |= base + t + 64 * k < last && !word_arrived<ST>(w[k]);
-        } while (__any(waits));
+                for (int k = 0; k < LOADS; ++k)
+                    w[k] = load_word(slot_word(ws, slot0 + min(base + t + 64 * k, last - 1)));
+#pragma unroll
+                for (int k = 0; k < LOADS; ++k)
+                    waits |= base + t + 64 * k < last && !word_arrived<ST>(w[k]);
+            }
+        } while (__any(waits) && rounds-- > 0);
+        const bool clears = CLEAR && rounds >= 0 && base + 64 * LOADS > last;   // uniform
 #pragma unroll
         for (int k = 0; k < LOADS; ++k) {
             const int64_t i = base + t + 64 * k;
-            if (i < last)
-                store_word(slot_word(ws, i), 0);
+            if (clears && i < last)
+                store_word(slot_word(ws, slot0 + i), 0);
             if (i <= last)
                 v = merge(v, i == last ? own : from_word<ST>(w[k]));
         }
     }
 }
 
+// Where `count` (at least 2) work-groups meet: each calls meet() with one
+// wavefront, its `index`, and in lane i < R its partial of row i (the slots are
+// [row][index] from slot0 on).  True (wave-uniform) in exactly one of them,
+// which then holds in lane t of v[i] the fold of row i's partials t, t + 64,
+// ... (LOADS of them in flight, twice as many where there are more rounds of
+// that), and has cleared the slots.
+//
+// The last work-group waits for the others' partials, but not for good: which
+// work-groups run at the same time is the hardware's choice, and another
+// kernel may hold the places that theirs need.  After `rounds` looks in vain
+// it puts a mark into every slot whose partial has not come, says in `pending`
+// how many marks it left, and is done.  A work-group that finds the mark where
+// it puts its partial counts itself off there, and the one that brings the
+// count to zero, the last, folds in the waiter's place: the same slots in the
+// same order.  So every wait ends, whatever runs when, and the result's bits do
+// not depend on it.  (Two runs that share their slots, which they must not,
+// get wrong numbers from that, and end.)
+//
+// To the others this costs an exchange that returns instead of a store, which
+// takes no longer (asum fp32 of 2^16, 2^18, 2^20 back to back in a HIP graph,
+// us: 2.49 2.55 3.07 with the store, 2.46 2.53 3.10 with the exchange).
+template <class ST, int R>
+struct Meeting {
+    char *ws;
+    unsigned *pending;
+    int64_t slot0, count, index;
+    ST own;
+    ST (&v)[R];
+
+    __device__ __forceinline__ uint64_t *slot(int64_t i) const { return slot_word(ws, slot0 + i); }
+
+    template <int LOADS>
+    __device__ __forceinline__ bool fold(int rounds)
+    {
+        const int64_t last = count - 1;
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            v[i] = zero_of<ST>();
+            const ST mine = lane_value(own, i);
+            if (i == R - 1)
+                fold_slots<ST, LOADS, true>(ws, slot0 + i * count, last, mine, rounds, v[i]);
+            else
+                fold_slots<ST, LOADS, false>(ws, slot0 + i * count, last, mine, rounds, v[i]);
+        }
+        if (__builtin_expect(rounds < 0, 0))
+            return false;
+        const int64_t left = (R - 1) * count + last / (64 * LOADS) * (64 * LOADS);   // not cleared on the way
+        for (int64_t i = threadIdx.x & 63; i < left; i += 64)
+            store_word(slot(i), 0);
+        return true;
+    }
+
+    // The waiter has waited in vain, or a work-group has found `marks` marks.
+    __device__ __forceinline__ bool hand_over(unsigned marks)
+    {
+        const int t = threadIdx.x & 63;
+        const int64_t last = count - 1;
+        if (index == last) {
+            if (t < R)
+                store_word(slot(t * count + last), to_word(own));
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            __builtin_amdgcn_s_waitcnt(0);   // its own partials are there before the marks count
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            marks = 0;
+            for (int64_t i = t; i < R * count; i += 64) {
+                uint64_t w = load_word(slot(i));
+                if (!word_arrived<ST>(w) && __hip_atomic_compare_exchange_strong(slot(i), &w, SLOT_MARK, __ATOMIC_RELAXED,
+                                                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                    --marks;
+            }
+#pragma unroll
+            for (int m = 1; m < 64; m <<= 1)
+                marks += __shfl_xor(marks, m, 64);
+        }
+        int finishes = 0;
+        if (t == 0)
+            finishes = __hip_atomic_fetch_add(pending, marks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + marks == 0;
+        if (!__builtin_amdgcn_readfirstlane(finishes))
+            return false;
+        // every partial is in its slot now
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        if (t < R)
+            own = from_word<ST>(load_word(slot(t * count + last)));
+        fold<1>(0);
+        if (t < R)
+            store_word(slot(t * count + last), 0);
+        return true;
+    }
+};
+
+template <int LOADS, class ST, int R>
+__device__ __forceinline__ bool meet(char *ws, unsigned *pending, int64_t slot0, int64_t count, int64_t index, ST own,
+                                     int rounds, ST (&v)[R])
+{
+    Meeting<ST, R> m{ws, pending, slot0, count, index, own, v};
+    const int t = threadIdx.x & 63;
+    unsigned marks = 0;
+    if (index != count - 1) {
+        bool marked = false;
+        if (t < R)
+            marked = __hip_atomic_exchange(m.slot(t * count + index), to_word(own), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT) == SLOT_MARK;
+        marks = __popcll(__ballot(marked));
+        if (__builtin_expect(marks == 0, 1))
+            return false;
+    } else {
+        bool all;
+        if constexpr (LOADS == 1)
+            all = m.template fold<1>(rounds);
+        else
+            all = count <= 64 * LOADS ? m.template fold<LOADS>(rounds) : m.template fold<2 * LOADS>(rounds);
+        if (__builtin_expect(all, 1))
+            return true;
+    }
+    return m.hand_over(marks);
+}
+
 // The work-group's partial wg (valid in thread 0; every thread calls this
 // after the work-group tree) goes to the combine: with one work-group it is
-// the result; else every work-group but the last of the grid stores it, tagged,
-// and is done, and one wavefront of the last one folds all partials as they
-// arrive -- lane t folds partials t, t + 64, t + 128, ... in that order
-// then the wave butterfly -- and writes the
-// result.  No barrier on this path.
+// the result; else one wavefront of each brings it to where they meet, and the
+// one that has them all -- lane t folded partials t, t + 64, t + 128, ... in
+// that order -- takes the wave butterfly and writes the result.  No barrier on
+// this path.
 //
-// The last work-group waits for the others, which wait for nothing: all of
-// them are dispatched before it, so they run or have run when it starts.
 // Against a wait for the store's completion, two levels of arrival counters
 // and the last arriver reading the slots (four dependent device-scope round
-// trips), this leaves the store's way and the read's.  Back to back in a HIP
+// trips), this leaves the partial's way and the read's.  Back to back in a HIP
 // graph, before and now (us): asum fp32 of 2^16 3.8 -> 2.9, 2^18 4.0 -> 3.2,
 // 2^20 4.6 -> 3.4, 2^24 14.0 -> 13.4; compensated bf16 of 2^22 5.9 -> 4.8.
 // The loads of a round are what the poll costs (each of the 64 lanes is its
@@ -423,29 +549,21 @@ __device__ __forceinline__ void combine_partials(const ReduceArgs &a, W wg)
     if (t >= 64)
         return;
     char *ws = reinterpret_cast<char *>(a.ws);
-    const int64_t last = (int64_t)gridDim.x - 1;
-    ST own = ST(wg);
-    if (blockIdx.x != last) {
-        if (t == 0) {
-            store_word(slot_word(ws, blockIdx.x), to_word(own));
-            stamp_arrival<STAMP>(a, 0);
-        }
-        return;
-    }
+    unsigned *pending = reinterpret_cast<unsigned *>(ws + WS_PENDING);
+    const int64_t count = gridDim.x;
     if (t == 0)
-        stamp_arrival<STAMP>(a, 1);
+        stamp_arrival<STAMP>(a, 0);
 
-    // the final reduce-seq o join, by this wavefront
-    own = first_lane(own);
-    ST v = zero_of<ST>();
-    if (last < 4 * 64)
-        fold_slots<ST, 4>(ws, last, own, v);
-    else
-        fold_slots<ST, 8>(ws, last, own, v);
-    v = wave_sum(v);
+    // the final reduce-seq o join, by one wavefront
+    ST v[1];
+    if (!meet<4>(ws, pending, 0, count, blockIdx.x, ST(wg), a.rounds, v))
+        return;
+    const ST total = wave_sum(v[0]);
     if (t == 0)
-        write_result(a.result, a.result_f64, v);
+        write_result(a.result, a.result_f64, total);
     if constexpr (STAMP) {
+        if (t == 0)
+            a.stamps[(int64_t)blockIdx.x * STAMPS_PER_WG + 6] |= 1ull << 32;
         __builtin_amdgcn_sched_barrier(0);
         stamp<STAMP>(a, 5);
     }

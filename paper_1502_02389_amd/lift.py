@@ -119,6 +119,7 @@ SIGNATURES = {
     "lift_stream_read": (_i32, [_i64, _vp, _vp, _kp, _vp]),
     "lift_stream_copy": (_i32, [_i64, _vp, _vp, _kp, _vp]),
     "lift_stamp_next_launch": (_i32, [_vp, _i64, ctypes.POINTER(ctypes.c_int32)]),
+    "lift_combine_rounds_next_launch": (_i32, [ctypes.c_int32]),
     "lift_dot_ex_noalloc": (_i32, [_i64, _i32, _vp, _vp, _i32, _i32, _vp, _kp, _vp]),
     "lift_default_knobs": (_i32, [ctypes.c_char_p, _i32, _i32, _i64, _i64, ctypes.c_char_p, ctypes.c_int32, _kp]),
 }
@@ -276,6 +277,11 @@ def lift_stamp_next_launch(stamps, capacity):
     khz = ctypes.c_int32(0)
     st = _lib().lift_stamp_next_launch(stamps, capacity, ctypes.byref(khz) if stamps else None)
     return st, khz.value
+
+
+def lift_combine_rounds_next_launch(rounds):
+    """Bound of the next combine's wait (see lift_combine_rounds_next_launch in lift.h)."""
+    return _lib().lift_combine_rounds_next_launch(rounds)
 
 
 def lift_status_string(status):
