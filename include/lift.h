@@ -234,6 +234,17 @@ lift_status lift_gemv(int64_t m, int64_t n, float alpha, const float *A, int64_t
 /* Bytes of workspace any asum/dot call (plain or _ex) needs on this device. */
 size_t lift_workspace_bytes(void);
 
+/* The workspace of the graph that `stream` is being captured into, or *ws =
+ * NULL where it is not being captured: zero-filled device memory of
+ * lift_workspace_bytes() bytes for the calls captured on this stream, the same
+ * at each call during one capture.  It belongs to the graph: it is allocated
+ * outside the capture, and given back when the graph, its clones and all their
+ * instances are destroyed.  So graphs captured on one stream may be replayed on
+ * several, next to each other and to calls that are not captured (two instances
+ * or clones of one graph share it and may not).  The current device must be
+ * the stream's.  LIFT_EINVAL: ws NULL. */
+lift_status lift_capture_workspace(hipStream_t stream, void **ws);
+
 /* Largest work-group count a reduction grid uses. */
 int32_t lift_max_workgroups(void);
 

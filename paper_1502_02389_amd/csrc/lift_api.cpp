@@ -1615,6 +1615,144 @@ lift_status batch_plan(const lift_problem *probs, int32_t count, int storage, in
 
 }  // namespace
 
+// ---- workspaces of graphs --------------------------------------------------
+
+namespace {
+
+// A graph may be replayed at any time, next to whatever else runs, so the calls
+// captured into it have a workspace that is the graph's own: one per capture
+// and stream, given back by the runtime when the graph and all its instances
+// are gone and none of their replays runs any more.
+struct GraphWorkspace {
+    unsigned long long capture;
+    hipStream_t stream;
+    int device;
+    void *mem;
+};
+
+// Never destroyed: graphs may end after this library's own statics have.
+struct GraphWorkspaces {
+    std::mutex mu;   // not held over a HIP call: the runtime calls give_back() on its own
+    std::vector<GraphWorkspace *> owned, spare;
+};
+
+// Given back and kept for later captures (164 KB each); more are freed.
+constexpr size_t SPARE_WORKSPACES = 32;
+
+GraphWorkspaces &graph_workspaces()
+{
+    static GraphWorkspaces *all = new GraphWorkspaces;
+    return *all;
+}
+
+void give_back(void *p)
+{
+    GraphWorkspaces &all = graph_workspaces();
+    std::lock_guard<std::mutex> lock(all.mu);
+    const auto at = std::find(all.owned.begin(), all.owned.end(), static_cast<GraphWorkspace *>(p));
+    if (at != all.owned.end()) {
+        all.spare.push_back(*at);
+        all.owned.erase(at);
+    }
+}
+
+// While one lives, this thread may allocate although a stream is captured
+// (what it does is on no captured stream).
+struct OutsideCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    OutsideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~OutsideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// Zeros in mem, on a stream of its own, when this returns.
+hipError_t zero_now(void *mem, size_t bytes)
+{
+    hipStream_t side = nullptr;
+    hipError_t e = hipStreamCreateWithFlags(&side, hipStreamNonBlocking);
+    if (e != hipSuccess)
+        return e;
+    e = hipMemsetAsync(mem, 0, bytes, side);
+    if (e == hipSuccess)
+        e = hipStreamSynchronize(side);
+    (void)hipStreamDestroy(side);
+    return e;
+}
+
+lift_status capture_workspace(hipStream_t stream, void **ws)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    hipGraph_t graph = nullptr;
+    hipError_t e = hipStreamGetCaptureInfo_v2(stream, &status, &id, &graph, nullptr, nullptr);
+    if (e != hipSuccess)
+        return hip_fail(e);
+    if (status != hipStreamCaptureStatusActive)
+        return LIFT_OK;
+    int dev = 0;
+    e = hipGetDevice(&dev);
+    if (e != hipSuccess)
+        return hip_fail(e);
+    GraphWorkspaces &all = graph_workspaces();
+    GraphWorkspace *mine = nullptr;
+    std::vector<GraphWorkspace *> over;
+    {
+        std::lock_guard<std::mutex> lock(all.mu);
+        for (const GraphWorkspace *w : all.owned)
+            if (w->capture == id && w->stream == stream && w->device == dev) {
+                *ws = w->mem;
+                return LIFT_OK;
+            }
+        for (size_t i = all.spare.size(); i-- > 0 && !mine;)
+            if (all.spare[i]->device == dev) {
+                mine = all.spare[i];
+                all.spare.erase(all.spare.begin() + (std::ptrdiff_t)i);
+            }
+        while (all.spare.size() > SPARE_WORKSPACES) {
+            over.push_back(all.spare.back());
+            all.spare.pop_back();
+        }
+    }
+    OutsideCapture outside;
+    for (GraphWorkspace *w : over) {
+        (void)hipFree(w->mem);
+        delete w;
+    }
+    if (!mine) {
+        mine = new (std::nothrow) GraphWorkspace{0, nullptr, dev, nullptr};
+        if (!mine)
+            return hip_fail(hipErrorOutOfMemory);
+        e = hipMalloc(&mine->mem, lift_workspace_bytes());
+    }
+    if (e == hipSuccess)
+        e = zero_now(mine->mem, lift_workspace_bytes());
+    if (e != hipSuccess) {
+        (void)hipFree(mine->mem);
+        delete mine;
+        return hip_fail(e);
+    }
+    mine->capture = id;
+    mine->stream = stream;
+    {
+        std::lock_guard<std::mutex> lock(all.mu);
+        all.owned.push_back(mine);
+    }
+    hipUserObject_t object = nullptr;
+    e = hipUserObjectCreate(&object, mine, give_back, 1, hipUserObjectNoDestructorSync);
+    if (e != hipSuccess)
+        give_back(mine);
+    else {
+        e = hipGraphRetainUserObject(graph, object, 1, hipGraphUserObjectMove);
+        if (e != hipSuccess)
+            (void)hipUserObjectRelease(object, 1);   // gives it back
+    }
+    if (e != hipSuccess)
+        return hip_fail(e);
+    *ws = mine->mem;
+    return LIFT_OK;
+}
+
+}  // namespace
+
 extern "C" {
 
 size_t lift_workspace_bytes(void) { return (size_t)(WS_HEADER + (int64_t)MAX_WORKGROUPS * WS_SLOT); }
@@ -2160,6 +2298,14 @@ lift_status lift_stamp_next_launch(uint64_t *stamps, int64_t capacity, int32_t *
     g_stamps = stamps;
     g_stamp_capacity = capacity;
     return LIFT_OK;
+}
+
+lift_status lift_capture_workspace(hipStream_t stream, void **ws)
+{
+    if (!ws)
+        return LIFT_EINVAL;
+    *ws = nullptr;
+    return stream ? capture_workspace(stream, ws) : LIFT_OK;   // the null stream cannot be captured
 }
 
 lift_status lift_combine_rounds_next_launch(int32_t rounds)

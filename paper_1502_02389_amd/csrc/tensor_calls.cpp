@@ -34,12 +34,13 @@ struct Entry {  // the C entry points, as addresses from the loaded library
                       const void *, void *);
     Status (*blackscholes)(int64_t, const float *, float, float, float, float, float *, const void *, void *);
     Status (*md)(int64_t, const float *, int64_t, const int32_t *, float, float, float, float *, const void *, void *);
+    Status (*capture_workspace)(void *, void **);
+    size_t (*workspace_bytes)(void);
 } entry;
 
 PyObject *raw_stream = nullptr;      // device index -> stream handle of the current stream
 PyObject *make_workspace = nullptr;  // device -> the (device, stream) workspace tensor
 PyObject *check_status = nullptr;    // (status, name): raises
-PyObject *is_capturing = nullptr;    // whether the current stream is being captured
 
 // The tensor behind a plain torch.Tensor on a GPU, contiguous; else null.
 const at::Tensor *gpu_tensor(PyObject *o)
@@ -108,22 +109,44 @@ bool current_stream(const at::Tensor &t, void **out)
     return !PyErr_Occurred();
 }
 
-// The workspace of (device, stream): the binding's own, held here too so that
-// the look-up of a stream met before is a short search.
+// The workspace of a call on a stream: the graph's own where the stream is
+// being captured, else that of (device, stream), the binding's own, held here
+// too so that the look-up of a stream met before is a short search.
 struct Workspace {
-    int64_t device;
-    void *stream;
     at::Tensor tensor;
+    void *at = nullptr;
+    size_t bytes = 0;
 };
 
-bool workspace(PyObject *tensor, const at::Tensor &t, void *stream, at::Tensor *out)
+bool workspace(PyObject *tensor, const at::Tensor &t, void *stream, Workspace *out)
 {
-    static std::vector<Workspace> *known = new std::vector<Workspace>();   // under the interpreter's lock
-    for (const Workspace &w : *known)
-        if (w.stream == stream && w.device == t.get_device()) {
-            *out = w.tensor;
-            return true;
-        }
+    struct Known {
+        int64_t device;
+        void *stream;
+        at::Tensor tensor;
+    };
+    static std::vector<Known> *known = new std::vector<Known>();   // under the interpreter's lock
+    const Status st = entry.capture_workspace(stream, &out->at);
+    if (st != 0) {
+        PyObject *r = PyObject_CallFunction(check_status, "is", st, "lift_capture_workspace");
+        Py_XDECREF(r);
+        if (r)
+            PyErr_SetString(PyExc_RuntimeError, "lift_capture_workspace");
+        return false;
+    }
+    if (out->at) {
+        out->bytes = entry.workspace_bytes();
+        return true;
+    }
+    const auto take = [&](const at::Tensor &ws) {
+        out->tensor = ws;
+        out->at = ws.data_ptr();
+        out->bytes = (size_t)ws.numel();
+        return true;
+    };
+    for (const Known &w : *known)
+        if (w.stream == stream && w.device == t.get_device())
+            return take(w.tensor);
     PyObject *dev = PyObject_GetAttrString(tensor, "device");
     if (!dev)
         return false;
@@ -135,8 +158,7 @@ bool workspace(PyObject *tensor, const at::Tensor &t, void *stream, at::Tensor *
         known->erase(known->begin());
     known->push_back({t.get_device(), stream, THPVariable_Unpack(ws)});
     Py_DECREF(ws);
-    *out = known->back().tensor;
-    return true;
+    return take(known->back().tensor);
 }
 
 PyObject *none()
@@ -186,7 +208,7 @@ PyObject *reduce(PyObject *xo, PyObject *yo, PyObject *acco, PyObject *dtype)
             return none();
     }
     void *stream = nullptr;
-    at::Tensor ws;
+    Workspace ws;
     if (!current_stream(*x, &stream) || !workspace(xo, *x, stream, &ws))
         return nullptr;
     at::Tensor result;
@@ -194,10 +216,9 @@ PyObject *reduce(PyObject *xo, PyObject *yo, PyObject *acco, PyObject *dtype)
         const int64_t n = x->numel();
         const int rc = rt == at::kDouble ? 3 : 0;
         result = at::empty({}, x->options().dtype(rt).requires_grad(false));
-        void *wp = ws.data_ptr();
-        const size_t wb = (size_t)ws.numel();
-        return y ? entry.dot(n, code, x->const_data_ptr(), y->const_data_ptr(), acc, rc, result.data_ptr(), wp, wb, nullptr, stream)
-                 : entry.asum(n, code, x->const_data_ptr(), acc, rc, result.data_ptr(), wp, wb, nullptr, stream);
+        return y ? entry.dot(n, code, x->const_data_ptr(), y->const_data_ptr(), acc, rc, result.data_ptr(), ws.at, ws.bytes,
+                             nullptr, stream)
+                 : entry.asum(n, code, x->const_data_ptr(), acc, rc, result.data_ptr(), ws.at, ws.bytes, nullptr, stream);
     });
     return finish(st, y ? "lift_dot" : "lift_asum", st == 0 ? THPVariable_Wrap(std::move(result)) : nullptr);
 }
@@ -264,24 +285,16 @@ PyObject *call_gemv(PyObject *const *args)   // alpha, A, x, beta, y, acc
     void *stream;
     if (!current_stream(*A, &stream))
         return nullptr;
-    // few long rows are split through the stream's workspace, but not under
-    // capture (as in the binding's own code, which takes 12 us whatever the
-    // size; through here, bf16: 8 x 33000 6.4, 22 x 60184 7.8, 8 x 65539 5.3 us)
-    at::Tensor ws;
-    if (cols * A->element_size() > 65536 && m <= 512) {
-        PyObject *capturing = PyObject_CallNoArgs(is_capturing);
-        if (!capturing)
-            return nullptr;
-        const int yes = PyObject_IsTrue(capturing);
-        Py_DECREF(capturing);
-        if (yes < 0 || (!yes && !workspace(args[1], *A, stream, &ws)))
-            return nullptr;
-    }
+    // few long rows are split through a workspace (the binding's own code takes
+    // 12 us whatever the size; through here, bf16: 8 x 33000 6.4, 22 x 60184
+    // 7.8, 8 x 65539 5.3 us)
+    Workspace ws;
+    if (cols * A->element_size() > 65536 && m <= 512 && !workspace(args[1], *A, stream, &ws))
+        return nullptr;
     const Status st = unlocked([&] {
-        if (ws.defined())
+        if (ws.at)
             return entry.gemv_ws(m, cols, alpha, code, A->const_data_ptr(), lda, x->const_data_ptr<float>(), beta,
-                                 static_cast<float *>(y->data_ptr()), acc, ws.data_ptr(), (size_t)ws.numel(), nullptr,
-                                 stream);
+                                 static_cast<float *>(y->data_ptr()), acc, ws.at, ws.bytes, nullptr, stream);
         return entry.gemv(m, cols, alpha, code, A->const_data_ptr(), lda, x->const_data_ptr<float>(), beta,
                           static_cast<float *>(y->data_ptr()), acc, nullptr, stream);
     });
@@ -358,13 +371,13 @@ PyObject *guarded(PyObject *, PyObject *const *args, Py_ssize_t n)
     }
 }
 
-// init(addresses of scal_ex, asum_ex, dot_ex, gemv_ex, blackscholes_ex, md_ex, gemv_ex_ws, raw_stream, workspace, check,
-// is_capturing)
+// init(addresses of scal_ex, asum_ex, dot_ex, gemv_ex, blackscholes_ex, md_ex, gemv_ex_ws, capture_workspace, workspace_bytes,
+// raw_stream, workspace, check)
 PyObject *init(PyObject *, PyObject *args)
 {
-    unsigned long long a[7];
-    PyObject *s, *w, *c, *g;
-    if (!PyArg_ParseTuple(args, "KKKKKKKOOOO", &a[0], &a[1], &a[2], &a[3], &a[4], &a[5], &a[6], &s, &w, &c, &g))
+    unsigned long long a[9];
+    PyObject *s, *w, *c;
+    if (!PyArg_ParseTuple(args, "KKKKKKKKKOOO", &a[0], &a[1], &a[2], &a[3], &a[4], &a[5], &a[6], &a[7], &a[8], &s, &w, &c))
         return nullptr;
     entry.scal = reinterpret_cast<decltype(entry.scal)>(a[0]);
     entry.asum = reinterpret_cast<decltype(entry.asum)>(a[1]);
@@ -373,18 +386,17 @@ PyObject *init(PyObject *, PyObject *args)
     entry.blackscholes = reinterpret_cast<decltype(entry.blackscholes)>(a[4]);
     entry.md = reinterpret_cast<decltype(entry.md)>(a[5]);
     entry.gemv_ws = reinterpret_cast<decltype(entry.gemv_ws)>(a[6]);
+    entry.capture_workspace = reinterpret_cast<decltype(entry.capture_workspace)>(a[7]);
+    entry.workspace_bytes = reinterpret_cast<decltype(entry.workspace_bytes)>(a[8]);
     Py_INCREF(s);
     Py_INCREF(w);
     Py_INCREF(c);
-    Py_INCREF(g);
     Py_XDECREF(raw_stream);
     Py_XDECREF(make_workspace);
     Py_XDECREF(check_status);
-    Py_XDECREF(is_capturing);
     raw_stream = s;
     make_workspace = w;
     check_status = c;
-    is_capturing = g;
     return none();
 }
 

@@ -95,6 +95,7 @@ SIGNATURES = {
     "lift_dot": (_i32, [_i64, _vp, _vp, _vp, _vp, _sz, _vp]),
     "lift_gemv": (_i32, [_i64, _i64, _f32, _vp, _i64, _vp, _f32, _vp, _vp]),
     "lift_workspace_bytes": (_sz, []),
+    "lift_capture_workspace": (_i32, [_vp, ctypes.POINTER(_vp)]),
     "lift_max_workgroups": (ctypes.c_int32, []),
     "lift_scal_ex": (_i32, [_i64, _f32, _vp, _vp, _kp, _vp]),
     "lift_asum_ex": (_i32, [_i64, _i32, _vp, _i32, _i32, _vp, _vp, _sz, _kp, _vp]),
@@ -171,10 +172,10 @@ def _native():
                 except ImportError:
                     native = _NoNative
                 else:
-                    names = ("scal_ex", "asum_ex", "dot_ex", "gemv_ex", "blackscholes_ex", "md_ex", "gemv_ex_ws")
+                    names = ("scal_ex", "asum_ex", "dot_ex", "gemv_ex", "blackscholes_ex", "md_ex", "gemv_ex_ws",
+                             "capture_workspace", "workspace_bytes")
                     at = [ctypes.cast(getattr(lib, f"lift_{n}"), ctypes.c_void_p).value for n in names]
-                    native.init(*at, torch._C._cuda_getCurrentRawStream, workspace, _ok,
-                                torch.cuda.is_current_stream_capturing)
+                    native.init(*at, torch._C._cuda_getCurrentRawStream, workspace, _ok)
                 _NATIVE = native
     return _NATIVE
 
@@ -279,6 +280,13 @@ def lift_stamp_next_launch(stamps, capacity):
     return st, khz.value
 
 
+def lift_capture_workspace(stream):
+    """(status, address or None) of the workspace of the graph that `stream` is being captured into."""
+    ws = ctypes.c_void_p()
+    st = _lib().lift_capture_workspace(stream, ctypes.byref(ws))
+    return st, ws.value
+
+
 def lift_combine_rounds_next_launch(rounds):
     """Bound of the next combine's wait (see lift_combine_rounds_next_launch in lift.h)."""
     return _lib().lift_combine_rounds_next_launch(rounds)
@@ -374,7 +382,9 @@ def workspace(device, stream=None):
     """The zero-initialised workspace for (device, stream), allocated once.
 
     Every asum/dot call leaves it zeroed again, so it is reused without a
-    memset; concurrent streams get their own.
+    memset; concurrent streams get their own.  For eager calls: a graph may be
+    replayed on any stream, so what is captured into it takes the graph's own
+    (``lift_capture_workspace``).
     """
     torch = _torch()
     device = torch.device(device)
@@ -383,9 +393,40 @@ def workspace(device, stream=None):
     with _WS_LOCK:
         ws = _WS.get(key)
         if ws is None:
-            ws = torch.zeros(lift_workspace_bytes(), dtype=torch.uint8, device=device)
+            if device.type == "cuda" and torch.cuda.is_current_stream_capturing():
+                ws = _zeros_outside_capture(lift_workspace_bytes(), device)
+            else:
+                ws = torch.zeros(lift_workspace_bytes(), dtype=torch.uint8, device=device)
             _WS[key] = ws
     return ws
+
+
+def _zeros_outside_capture(nbytes, device):
+    """Zeroed device memory while the current stream is being captured: filled
+    now, not when the graph is replayed, and not from the graph's pool."""
+    torch = _torch()
+    exchange = ctypes.CDLL("libamdhip64.so").hipThreadExchangeStreamCaptureMode
+    mode = ctypes.c_int(2)                       # hipStreamCaptureModeRelaxed
+    exchange(ctypes.byref(mode))
+    try:
+        side = torch.cuda.Stream(device)
+        with torch.cuda.stream(side):
+            t = torch.zeros(nbytes, dtype=torch.uint8, device=device)
+        side.synchronize()
+    finally:
+        exchange(ctypes.byref(mode))
+    return t
+
+
+def _call_workspace(device, stream):
+    """(address, bytes) of the workspace of a call on `stream`, the current
+    stream of `device`: the graph's own where it is being captured."""
+    st, at = lift_capture_workspace(stream)
+    _ok(st, "lift_capture_workspace")
+    if at:
+        return at, lift_workspace_bytes()
+    ws = workspace(device)
+    return ws.data_ptr(), ws.numel()
 
 
 _DT = None
@@ -448,16 +489,16 @@ def _reduce(which, x, y, acc, result_dtype, knobs):
         if y.device != x.device:
             raise ValueError("x and y must be on the same device")
     result = torch.empty((), dtype=result_dtype, device=x.device)
-    ws = workspace(x.device)
     s = _stream_handle(x.device)
+    ws, ws_bytes = _call_workspace(x.device, s)
     accc = ACC[acc] if isinstance(acc, str) else int(acc)
     rt = _dtype_code(result_dtype)
     if which == "asum":
         st = lift_asum_ex(x.numel(), _dtype_code(x.dtype), x.data_ptr(), accc, rt, result.data_ptr(),
-                          ws.data_ptr(), ws.numel(), knobs, s)
+                          ws, ws_bytes, knobs, s)
     else:
         st = lift_dot_ex(x.numel(), _dtype_code(x.dtype), x.data_ptr(), y.data_ptr(), accc, rt,
-                         result.data_ptr(), ws.data_ptr(), ws.numel(), knobs, s)
+                         result.data_ptr(), ws, ws_bytes, knobs, s)
     _ok(st, f"lift_{which}")
     return result
 
@@ -553,13 +594,11 @@ def gemv(alpha, A, x, beta, y, acc="f32", knobs=None, lda=None):
         raise ValueError("y must have one entry per row of A")
     s = _stream_handle(A.device)
     accc = ACC[acc] if isinstance(acc, str) else int(acc)
-    if n * A.element_size() > 65536 and m <= 512 and not torch.cuda.is_current_stream_capturing():
-        # few long rows: split over work-groups through the stream's
-        # workspace.  Not under capture: a graph may be replayed on another
-        # stream, next to work that uses the same workspace.
-        ws = workspace(A.device)
+    if n * A.element_size() > 65536 and m <= 512:
+        # few long rows: split over work-groups through a workspace
+        ws, ws_bytes = _call_workspace(A.device, s)
         st = lift_gemv_ex_ws(m, n, float(alpha), _dtype_code(A.dtype), A.data_ptr(), lda, x.data_ptr(),
-                             float(beta), y.data_ptr(), accc, ws.data_ptr(), ws.numel(), knobs, s)
+                             float(beta), y.data_ptr(), accc, ws, ws_bytes, knobs, s)
     else:
         st = lift_gemv_ex(m, n, float(alpha), _dtype_code(A.dtype), A.data_ptr(), lda, x.data_ptr(),
                           float(beta), y.data_ptr(), accc, knobs, s)
