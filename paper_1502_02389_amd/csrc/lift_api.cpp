@@ -1130,8 +1130,11 @@ bool batch_choose(const lift_problem *probs, int32_t count, int storage, int acc
     const void *kern = nullptr;
     int64_t groups = 0, filled = 0;
     int cus = 0;
-    if (batch_wave_groups(storage, acc, &kern, &groups) != LIFT_OK || cu_count(&cus) != LIFT_OK)
-        return false;  // no device: the plan itself reports that
+    const int error = g_last_hip_error;
+    if (batch_wave_groups(storage, acc, &kern, &groups) != LIFT_OK || cu_count(&cus) != LIFT_OK) {
+        g_last_hip_error = error;  // no device: the plan itself reports that, if its problems are in order
+        return false;
+    }
     const int eb = elem_bytes(storage);
     const double total = batch_reads(probs, count, eb, &filled);
     if (total <= BATCH_WAVE_SHARE * 4 * groups)
