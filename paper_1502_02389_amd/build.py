@@ -2,7 +2,10 @@
 
 ``python -m paper_1502_02389_amd.build`` compiles every translation unit under
 ``csrc/`` in parallel into ``_build/`` and links the shared library next to
-this file, and the binding's native route (``_tensor_calls.so``, g++) beside it.  All device code is compiled with packed-FP32 instructions
+this file; that takes hipcc alone.  Where torch, Python's headers and a C++
+compiler are there too, the binding's native route (``_tensor_calls.so``) is
+built beside it; without it the tensor calls take the binding's own, slower
+code.  All device code is compiled with packed-FP32 instructions
 disabled and without floating-point contraction (fma is written explicitly
 where the arithmetic wants it).
 
@@ -152,6 +155,18 @@ def build_tensor_calls() -> str:
     return TENSOR_CALLS
 
 
+def native_route() -> str | None:
+    """The native route, or None if it cannot be built here: that is reported,
+    and none of an earlier build is left behind."""
+    try:
+        return build_tensor_calls()
+    except Exception as e:   # no torch, no headers, no compiler, or it refuses the source
+        if os.path.exists(TENSOR_CALLS):
+            os.remove(TENSOR_CALLS)
+        print(f"{os.path.basename(TENSOR_CALLS)} is not built, the tensor calls go without it: {e}", file=sys.stderr)
+        return None
+
+
 def _compile(src: str, sanitize: bool = False) -> str:
     obj = os.path.join(SAN_BUILD if sanitize else BUILD, os.path.splitext(src)[0] + ".o")
     cmd = [HIPCC, *CFLAGS, *(SAN_FLAGS if sanitize else []), "-c", os.path.join(CSRC, src), "-o", obj]
@@ -174,10 +189,9 @@ def build(jobs: int | None = None, verbose: bool = False, sanitize: bool = False
     srcs = sources()
     jobs = jobs or min(len(srcs), max(1, min(os.cpu_count() or 1, 16)))
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
-        calls = None if sanitize else ex.submit(build_tensor_calls)
+        if not sanitize:
+            ex.submit(native_route)
         objs = list(ex.map(lambda f: _compile(f, sanitize), srcs))
-        if calls is not None:
-            calls.result()
     tmp = lib + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -157,6 +157,32 @@ class _NoNative:
 
 
 _NATIVE = None
+_INTERFACE = 2   # of csrc/tensor_calls.cpp's init()
+
+
+def _load_native():
+    """The extension, or _NoNative: silently where it is not built, with a
+    warning where what is there does not load or is of another build."""
+    import importlib
+    import warnings
+
+    name = f"{__package__}._tensor_calls"
+    try:
+        native = importlib.import_module(name)
+    except ModuleNotFoundError as e:
+        if e.name == name:
+            return _NoNative
+        why = e
+    except ImportError as e:
+        why = e
+    else:
+        found = getattr(native, "INTERFACE", None)
+        if found == _INTERFACE:
+            return native
+        why = f"its interface is {found}, not {_INTERFACE}"
+    warnings.warn(f"the native route of the tensor calls is left out ({why}); build the package again", RuntimeWarning,
+                  stacklevel=4)
+    return _NoNative
 
 
 def _native():
@@ -167,11 +193,8 @@ def _native():
         lib, torch = _lib(), _torch()
         with _LOCK:
             if _NATIVE is None:
-                try:
-                    from . import _tensor_calls as native
-                except ImportError:
-                    native = _NoNative
-                else:
+                native = _load_native()
+                if native is not _NoNative:
                     names = ("scal_ex", "asum_ex", "dot_ex", "gemv_ex", "blackscholes_ex", "md_ex", "gemv_ex_ws",
                              "capture_workspace", "workspace_bytes")
                     at = [ctypes.cast(getattr(lib, f"lift_{n}"), ctypes.c_void_p).value for n in names]
