@@ -161,15 +161,18 @@ typedef enum lift_lane_form {
  *      size bucket floor(log2(elements)) (gemv: m n, and floor(log2(n)) of
  *      its rows; MD: n k; a batch: one bucket) -- a table built into the library from the autotuner's
  *      cache, used only on a device of the architecture and compute-unit
- *      count it was tuned on;
+ *      count it was tuned on (and not where the environment variable
+ *      LIFT_IGNORE_TUNED is set, read once per process);
  *   3. else the library defaults (gemv: also where the tuned knobs' vector
  *      loads do not fit A's row starts and x's alignment, or a row takes more
  *      steps of them than the power of two they were tuned on; its launch then
  *      goes by row length, for any alignment, as it does for all-zero knobs;
  *      dot: also where x and y lie in different 16-byte phases, whose launch
- *      without knobs then reads both in vectors).
- * lift_default_knobs reports which applies.  Explicit knobs are never
- * overridden. */
+ *      without knobs then reads both in vectors; a batch takes its reduction
+ *      split from its size and up to 64 KiB per wavefront has another form, see
+ *      lift_kind).  Some of these launches have no knob set that gives them.
+ * lift_default_knobs reports which applies by op and sizes.  Explicit knobs are
+ * never overridden. */
 typedef struct lift_knobs {
     int32_t block;         /* work-group size: 64, 128, 256, 512 or 1024
                               (1 to 32 too for the sequential lane forms)
@@ -512,12 +515,14 @@ lift_status lift_stamp_next_launch(uint64_t *stamps, int64_t capacity, int32_t *
  * rounds < 0. */
 lift_status lift_combine_rounds_next_launch(int32_t rounds);
 
-/* The knobs a call with knobs == NULL would run with on a device of
+/* The knobs that a call with knobs == NULL goes by on a device of
  * architecture `arch` (e.g. "gfx950"; NULL = the current device, a HIP
  * query) with `cus` compute units (ignored when arch is NULL): op is one of
  * "scal", "asum", "dot", "gemv", "batch", "blackscholes", "md"; elements is
  * the size the bucket is taken of (see lift_knobs); row_length is gemv's n
  * (its entries are also keyed by floor(log2(n)); ignored for other ops).
+ * Alignment and a batch's problems are not known here: where they lead past
+ * the tuned entry (see lift_knobs), the launch is another.
  * Fills *out (all zero = the library defaults) and returns 2 if
  * LIFT_FORCE_CONFIG applies, 1 for a tuned entry, 0 for the defaults;
  * LIFT_EINVAL for an unknown op, storage or accumulation, a null pointer,

@@ -354,6 +354,13 @@ const Forced &forced_config()
     return f;
 }
 
+// LIFT_IGNORE_TUNED set: calls without knobs go without tuned entries too.
+bool ignore_tuned()
+{
+    static const bool set = std::getenv("LIFT_IGNORE_TUNED") != nullptr;
+    return set;
+}
+
 // Architecture name (up to the first ':') and CU count of the current
 // device, cached per device; false if the device cannot be queried.
 bool device_identity(const char **arch, int *cus)
@@ -397,7 +404,7 @@ const lift_knobs *effective_knobs(const lift_knobs *given, int op, int storage, 
     }
     const char *arch = nullptr;
     int cus = 0;
-    if (!device_identity(&arch, &cus))  // no device: defaults (the launch reports the HIP error)
+    if (ignore_tuned() || !device_identity(&arch, &cus))  // no device: defaults (the launch reports the HIP error)
         return nullptr;
     const TunedEntry *e = tuned_entry(arch, cus, op, storage, acc, elements, row_length);
     return e ? &e->knobs : nullptr;
@@ -2252,6 +2259,8 @@ int32_t lift_default_knobs(const char *op, lift_dtype storage, lift_acc acc, int
     }
     if (!arch && !device_identity(&arch, &cus))
         return LIFT_EHIP;
+    if (ignore_tuned())
+        return 0;
     const TunedEntry *e = tuned_entry(arch, cus, top, storage, acc, elements, row_length);
     if (!e)
         return 0;

@@ -7,9 +7,15 @@ it times every point of a knob grid -- work-group size, bytes per load
 (asVector width), loads in flight per lane, split factor (elements per
 work-group), rows per wavefront for gemv -- and keeps the fastest.
 
-Timing: back-to-back launches bracketed by one HIP event pair on the stream
-the kernels run on, operands rotated over enough copies (>= 1 GiB) that no
-launch finds them in the 256 MB Infinity Cache; best of `trials` repeats.
+The library's own choice for the shape (a call without knobs, tuned entries
+left aside) is a candidate too: several of its launches have no knob set.  A
+knob set is kept only if it beats that choice by more than 2 %; else the
+shape gets no entry, and ``--write`` takes out one that is there.
+
+Timing: launches replayed from a HIP graph (a small one is shorter than its
+host call) and bracketed by one HIP event pair, operands rotated over enough
+copies (>= 1 GiB) that no launch finds them in the 256 MB Infinity Cache;
+median of `trials` repeats.
 
 Results persist in a JSON cache of entries keyed by ``op/storage/acc/bucket``
 (bucket = floor(log2(elements))), recorded for one device: its architecture
@@ -36,6 +42,7 @@ from . import lift as B
 
 DEFAULT_CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuning.json")
 COLD_BYTES = 1 << 30
+KEEP = 0.98   # a knob set's time against the library's own choice
 
 STORAGE_BYTES = {"f32": 4, "bf16": 2, "f16": 2}
 STORAGE_CODE = {"f32": B.LIFT_F32, "bf16": B.LIFT_BF16, "f16": B.LIFT_F16}
@@ -104,9 +111,11 @@ def lookup(op: str, storage: str, acc: str, elements: int, device=None, row_leng
 
 
 def save_cache(entries: dict, meta: dict, path: str | None = None):
+    """Merge entries into the cache; None takes the key's entry out."""
     path = path or cache_path()
     data = load_cache(path)
-    data.setdefault("entries", {}).update(entries)
+    merged = {**data.get("entries", {}), **entries}
+    data["entries"] = {k: e for k, e in merged.items() if e is not None}
     data["device"] = meta
     out = {k: v for k, v in data.items() if k != "_path"}
     tmp = path + ".tmp"
@@ -257,7 +266,6 @@ class Operands:
             self.bytes = per
             self.res = torch.zeros((), dtype=torch.float64, device=dev)
         self.ws = B.workspace(dev)
-        self.stream = torch.cuda.current_stream(dev).cuda_stream
 
     def call(self, i, acc, k):
         s = self.stream
@@ -282,22 +290,31 @@ class Operands:
             raise B.LiftError(st, f"tune {self.op}")
 
     def time_us(self, acc, k, reps=40, trials=5):
-        """Median over `trials` of the average time of `reps` back-to-back
-        calls that rotate over the operand sets (cold Infinity Cache)."""
+        """Median over `trials` of the average time of `reps` calls, replayed
+        from a graph, that rotate over the operand sets (cold Infinity Cache)."""
         import torch
 
-        for i in range(4):
-            self.call(i % self.sets, acc, k)
+        stream = torch.cuda.Stream()
+        self.stream = stream.cuda_stream
+        stream.wait_stream(torch.cuda.current_stream())
+        graph = torch.cuda.CUDAGraph()
         times = []
-        for _ in range(trials):
-            torch.cuda.synchronize()
-            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            e0.record()
-            for i in range(reps):
+        with torch.cuda.stream(stream):
+            for i in range(4):
                 self.call(i % self.sets, acc, k)
-            e1.record()
-            torch.cuda.synchronize()
-            times.append(e0.elapsed_time(e1) * 1e3 / reps)
+            stream.synchronize()
+            with torch.cuda.graph(graph, stream=stream):
+                for i in range(reps):
+                    self.call(i % self.sets, acc, k)
+            graph.replay()
+            for _ in range(trials):
+                stream.synchronize()
+                e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                e0.record(stream)
+                graph.replay()
+                e1.record(stream)
+                stream.synchronize()
+                times.append(e0.elapsed_time(e1) * 1e3 / reps)
         return sorted(times)[len(times) // 2]
 
 
@@ -320,7 +337,9 @@ def derived(op: str, storage: str, elements: int = None, n: int = None):
 def tune_one(op, storage, acc, elements=None, m=None, n=None, quick=False, log=None, space="grid"):
     """Search one call shape over the fixed grid or, for asum / dot with
     space="derived", over the kernels of the derived expressions; returns
-    (best entry, all results)."""
+    (best entry, all results).  The best entry also has "own_us", the time of
+    the library's own choice, where this process leaves tuned entries aside
+    (the command line does), and then "better" says whether it is to be kept."""
     ops = BatchOperands(storage) if op == "batch" else Operands(op, storage, elements, m, n)
     accc = acc if op == "batch" else B.ACC[acc]
     if space == "derived":
@@ -356,6 +375,11 @@ def tune_one(op, storage, acc, elements=None, m=None, n=None, quick=False, log=N
     best = {"knobs": kn, "us": round(us, 3), "GB_s": round(gbs, 1), "bytes": ops.bytes}
     if d is not None:
         best["expression"] = str(d.expr)
+    if os.environ.get("LIFT_IGNORE_TUNED"):
+        pairs = [(ops.time_us(accc, None), ops.time_us(accc, B.knobs(**kn))) for _ in range(3)]
+        own, tuned = (sorted(p[i] for p in pairs)[1] for i in (0, 1))
+        best["own_us"] = round(own, 3)
+        best["better"] = tuned < KEEP * own
     return best, [r[:3] for r in results]
 
 
@@ -376,6 +400,7 @@ def main(argv=None):
 
     import torch
 
+    os.environ["LIFT_IGNORE_TUNED"] = "1"   # read by the library at its first call without knobs
     props = torch.cuda.get_device_properties(0)
     arch, cus = current_device()
     meta = {"name": props.name, "arch": arch, "cus": cus, "lib": B.lift_version()}
@@ -405,8 +430,8 @@ def main(argv=None):
                                              log=log if args.verbose else None, space=args.space)
                         elements, row_length = shp[0], 0
                     k = key(op, storage, acc, elements, row_length)
-                    entries[k] = best
-                    log(f"== {k}: best {best}")
+                    entries[k] = best if best.pop("better", True) else None
+                    log(f"== {k}: best {best}" + ("" if entries[k] else ": no entry, the library's own choice is as fast"))
                     for us, kn, gbs in res[: args.top]:
                         log(f"   {us:8.2f} us {gbs:7.0f} GB/s {kn}")
                     log(f"   ({len(res)} points; slowest {res[-1][0]:.2f} us)")
