@@ -347,7 +347,7 @@ lift_status lift_blackscholes_ex(int64_t n, const float *s, float strike, float 
  * Binary32 throughout;
  * the sum over a list is split over the lanes given by lanes_per_item, in a
  * fixed order (deterministic).  Without knobs, systems of 2 to 4 times 5 MB of
- * positions run as several launches (an armed timing hook spans them): the
+ * positions with lists of at least 96 (2) or 64 slots run as several launches (an armed timing hook spans them): the
  * particles whose neighbours' indices are far from their own are summed a
  * slice of positions at a time, `force` holding the sums so far.  LIFT_EINVAL for bad sizes, pointers or
  * parameters; n must be below 2^31, and n * lanes_per_item (one thread per

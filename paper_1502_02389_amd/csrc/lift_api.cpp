@@ -1943,13 +1943,13 @@ lift_status lift_blackscholes(int64_t n, const float *s, float strike, float rat
 // MD in passes over slices of the positions (md_packed_kernel): the particles
 // whose neighbours lie near them are done by the first launch, the others
 // marked, and each pass adds their neighbours in one slice.  v: indices per
-// load of the first launch.
-static lift_status md_passes(const MdArgs &args, int slices, int v, hipStream_t stream)
+// load; kn: lanes and loads in flight of the first launch.
+static lift_status md_passes(const MdArgs &args, int slices, int v, const Knobs &kn, hipStream_t stream)
 {
     MdArgs a = args;
     const int64_t span = (a.n + slices - 1) / slices;
-    a.near = (uint32_t)(span / 2);
-    const void *sort = md_sort_kernel_table(v), *packed = md_packed_kernel_table(std::min(v, 2));
+    a.near = (uint32_t)(a.n / 12);
+    const void *sort = md_sort_kernel_table(kn.lanes, v, kn.unroll), *packed = md_packed_kernel_table(std::min(v, 2));
     if (!sort || !packed)
         return LIFT_EUNSUPPORTED;
     int cus = 0, fit = 1;
@@ -1959,13 +1959,13 @@ static lift_status md_passes(const MdArgs &args, int slices, int v, hipStream_t 
     if (st != LIFT_OK)
         return st;
     // 4 work-groups per CU: the lists' and the gathers' lines compete for the
-    // L1's outstanding misses, more wavefronts only add to that (3 slices:
-    // 4 per CU 772, 6: 785, 8: 837 us)
+    // L1's outstanding misses, more wavefronts change nothing (3 slices of 2^20
+    // particles, us: 2 per CU 1023, 3: 839, 4: 795, 6: 798, 8: 791)
     const int64_t grid = std::min<int64_t>((a.n + 15) / 16, (int64_t)cus * std::min(fit, 4));
     // an armed timing hook spans the launches
     const hipEvent_t t0 = g_time_start, t1 = g_time_stop;
     g_time_stop = nullptr;
-    st = launch(sort, (a.n * 8 + 255) / 256, 256, &a, stream);
+    st = launch(sort, (a.n * kn.lanes + 255) / 256, 256, &a, stream);
     for (int p = 0; p < slices && st == LIFT_OK; ++p) {
         MdPackedArgs s;
         s.md = a;
@@ -2005,18 +2005,6 @@ lift_status lift_md_ex(int64_t n, const float *pos, int64_t k, const int32_t *nb
     st = resolve(knobs, DEF_MD, 4, &kn);
     if (st != LIFT_OK)
         return st;
-    if (choose && !knobs) {
-        // 16 lanes per particle while 8 would leave wavefront slots empty
-        // (12288 particles, 128 slots: 5.9 against 6.6 us), else 8 (176400:
-        // 28 against 31 us in lattice order, 67 against 70 in random order),
-        // with as many loads in flight as cover a row and no more (a load past
-        // the row still costs its pairs' arithmetic: 38 us)
-        const int64_t kv = (k + 3) / 4;
-        kn.lanes = n < 65536 && kv >= 16 ? 16 : 8;
-        kn.unroll = 1;
-        while (kn.unroll < 4 && (int64_t)kn.lanes * kn.unroll < kv)
-            kn.unroll *= 2;
-    }
     if (kn.vec_bytes < 4 || kn.unroll > 4)
         return LIFT_EINVAL;
     // one thread per lane of each particle (16 lanes where the library chooses)
@@ -2028,6 +2016,22 @@ lift_status lift_md_ex(int64_t n, const float *pos, int64_t k, const int32_t *nb
     int v = kn.vec_bytes / 4;
     while (v > 1 && (k % v != 0 || !aligned(nbr, (size_t)v * 4)))
         v /= 2;
+    if (choose && !knobs) {
+        // 8 lanes per particle, with as many loads in flight as cover a row
+        // and no more (a load past the row still costs its pairs' arithmetic);
+        // 16 with two loads in flight for longer rows while 8 would leave
+        // wavefront slots empty, and where an index vector is not 4 of them
+        // (graph replays, us, random and lattice order, 16 lanes | 8: 32768 x 24
+        // 6.5 5.4 | 5.5 3.5, 262144 x 32 50.9 26.4 | 46.2 17.0, 262144 x 256 330
+        // 120 | 327 109; but 12288 x 128 5.9 | 6.6 in random order, and rows of 65,
+        // 343000 x 65 164.9 64.1 | 177.0 71.8).
+        const int64_t vecs = k / v;
+        const bool wide = n < 65536 ? vecs >= 16 : v < 4 && vecs > 16;
+        kn.lanes = wide ? 16 : 8;
+        kn.unroll = wide && v < 4 ? 2 : 1;
+        while (kn.unroll < (v < 4 ? 2 : 4) && (int64_t)kn.lanes * kn.unroll < vecs)
+            kn.unroll *= 2;
+    }
     const void *kern = md_kernel_table(kn.lanes, v, kn.unroll);
     if (!kern)
         return LIFT_EUNSUPPORTED;
@@ -2042,12 +2046,19 @@ lift_status lift_md_ex(int64_t n, const float *pos, int64_t k, const int32_t *nb
     a.eps24 = (float)(24.0 * (double)epsilon);
     a.near = 0;
     // Slices of about 5 MB of positions (an XCD's L2 holds 4 MiB), where there
-    // are 2 to 4 of them: up to 6 MB one pass is faster (512000 particles in
-    // random order, 8.2 MB: 363 us, 2 slices 300 us), and beyond 4 the lists'
-    // extra readings cost what the misses did.
+    // are 2 to 4 of them: below 7.5 MB one pass is as fast (474552 particles in
+    // random order, 7.6 MB, 128 slots: 316 us, 2 slices 284 us), and beyond 4
+    // the lists' extra readings cost what the misses did.
     const int slices = (int)std::min<int64_t>(5, (n * 16 + 2500000) / 5000000);
-    if (choose && k > 0 && slices >= 2 && slices <= 4)
-        return md_passes(a, slices, v, stream);
+    // A pass costs its reading of the lists and of the marks, whatever they
+    // hold; a gather costs by neighbours.  So short lists take one pass (2^20
+    // particles in random order, full lists, us, one pass | passes: of 16 222 |
+    // 530, of 40 551 | 560, of 48 656 | 587, of 64 879 | 651; lists of 64 that are
+    // 5/8 full 565 | 571; 512000 particles: of 64 291 | 267 and, 5/8 full, 191 |
+    // 212, of 96 433 | 348 and 285 | 272).
+    const bool long_lists = k >= (slices == 2 ? 96 : 64);
+    if (choose && !knobs && slices >= 2 && slices <= 4 && long_lists)
+        return md_passes(a, slices, v, kn, stream);
     const int64_t threads = n * kn.lanes;
     const int64_t grid = (threads + kn.block - 1) / kn.block;
     return launch(kern, grid, kn.block, &a, stream);

@@ -43,7 +43,7 @@ struct MdPackedArgs {
     uint32_t hi;
 };
 
-const void *md_sort_kernel_table(int v);
+const void *md_sort_kernel_table(int lanes, int v, int unroll);
 const void *md_packed_kernel_table(int v);
 const void *blackscholes_kernel_table(int vec_bytes, int unroll);
 const void *md_kernel_table(int lanes, int v, int unroll);

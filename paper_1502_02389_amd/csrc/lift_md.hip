@@ -80,9 +80,10 @@ __device__ __forceinline__ void add_pair(const MdArgs &a, const f32x4 &p, const 
 }
 
 // SORT: the first of several launches (see md_packed_kernel).  A wavefront
-// whose first particle lists a neighbour (among its first 32) that is more
-// than half a slice of positions away leaves its particles to the passes,
-// marked by their lists' length in the fourth component of their forces.
+// most of whose first particle's neighbours (of the first 32) have indices more
+// than n / 12 from its own leaves its particles to the passes, marked by their
+// lists' length in the fourth component of their forces.  In random order five
+// in six are that far; in a lattice's order only those beyond a periodic face.
 template <int L, int V, int U, bool SORT = false>
 __global__ void __launch_bounds__(1024) md_kernel(MdArgs a)
 {
@@ -94,9 +95,11 @@ __global__ void __launch_bounds__(1024) md_kernel(MdArgs a)
         return;
     if constexpr (SORT) {
         const int lane = threadIdx.x & 63;
-        const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)i), half = a.near;
+        const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)i), near = a.near;
         const uint32_t id = lane < 32 && lane < a.k ? (uint32_t)a.nbr[first * a.k + lane] : ~0u;
-        if (__ballot(id < (uint32_t)a.n && id - (first - half) > 2 * half)) {
+        const bool used = id < (uint32_t)a.n;
+        const int far = __popcll(__ballot(used && id - (first - near) > 2 * near));
+        if (2 * far > __popcll(__ballot(used))) {
             if (sub == 0)
                 reinterpret_cast<f32x4 *>(a.force)[i] = f32x4{0.f, 0.f, 0.f, (float)a.k};
             return;
@@ -150,9 +153,12 @@ __global__ void __launch_bounds__(1024) md_kernel(MdArgs a)
 // a position is 16 bytes, the line it comes in 128 (2^20 particles in random
 // order: 65.7 M misses, 8.4 GB for 0.57 GB of lists, positions and forces,
 // 1090 us).  Each pass wants only the neighbours in one slice of the
-// positions, which then stays in the L2, and adds to the force; reading the
-// lists again costs about 107 us per pass there, so three slices of 5.6 MB do
-// best (2: 880, 3: 765, 4: 840, 6: 1050 us).
+// positions, which then stays in the L2, and adds to the force; a further pass
+// costs 70 to 130 us there, most of it for reading the lists again, so three
+// slices of 5.6 MB do best (one pass 1088, 2 slices 896, 3: 796, 4: 868, 6: 1136
+// us).  Systems in a lattice's order pay 4 us per pass that finds no mark (2^20
+// particles, 80 neighbours in lists of 128: 163 us, one pass of 8 lanes 150, of
+// 16 lanes 170).
 //
 // A wavefront takes blocks of four marked particles (md_kernel's SORT form).
 // It first packs the wanted neighbours of each list in LDS -- 64 lanes over
@@ -162,9 +168,10 @@ __global__ void __launch_bounds__(1024) md_kernel(MdArgs a)
 // pair's arithmetic.  It reads the marks of 64 of its blocks at once: with
 // none marked a pass costs one round trip.
 //
-// A mark is the number of leading indices of the list that this pass has to
-// read: each pass leaves the place of the last neighbour in a later slice, so
-// padding and what is done are not read again, and the last pass leaves 0
+// A block's mark, in each of its particles' forces, is the number of leading
+// indices of its lists that this pass has to read: each pass leaves the place
+// of the last neighbour in a later slice, so padding and what is done are not
+// read again, and the last pass leaves 0
 // (2^20 particles, 80 neighbours in lists of 128: 803 us without, 795 with:
 // the L1's outstanding requests bound a pass, not bytes, nor round trips --
 // gathers for 64 packed indices at once instead of 32: 810).  Lists are far
@@ -185,30 +192,27 @@ __global__ void __launch_bounds__(256) md_packed_kernel(MdPackedArgs s)
     const f32x4 *pos = reinterpret_cast<const f32x4 *>(a.pos);
     f32x4 *force = reinterpret_cast<f32x4 *>(a.force);
 
-    int64_t base = 0;          // of this wave's blocks base .. base + 63: `need` the longest mark (lane j: block
+    const auto block = [&](int64_t j) { return wave + j * nwaves; };   // the wave's j-th
+    int64_t base = 0;          // of this wave's blocks base .. base + 63: `need` the mark (lane j: block
     int need = 0;              // base + j), `mask` which are to be done
     uint64_t mask = 0;
     const auto fill = [&] {
-        const int64_t b = min(wave + (base + lane) * nwaves, nblocks);
-        float most = 0.f;
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-            most = fmaxf(most, force[min(b * 4 + g, a.n - 1)][3]);
-        need = b < nblocks ? (int)most : 0;
+        const int64_t b = block(base + lane);
+        need = b < nblocks ? (int)force[b * 4][3] : 0;
         mask = __ballot(need > 0);
     };
     int len = 0;                                 // the block's index vectors
     const auto next_block = [&]() -> int64_t {   // wave-uniform; -1: none left
         while (mask == 0) {
             base += 64;
-            if (wave + base * nwaves >= nblocks)
+            if (block(base) >= nblocks)
                 return -1;
             fill();
         }
         const int j = __builtin_ctzll(mask);
         mask &= mask - 1;
         len = (__builtin_amdgcn_readlane(need, j) + V - 1) / V;
-        return wave + (base + j) * nwaves;
+        return block(base + j);
     };
 
     IV iv[4][U];
@@ -292,7 +296,7 @@ __global__ void __launch_bounds__(256) md_packed_kernel(MdPackedArgs s)
             fx = group_sum<L>(fx);
             fy = group_sum<L>(fy);
             fz = group_sum<L>(fz);
-            const int mark = grp & 2 ? (grp & 1 ? later[3] : later[2]) : (grp & 1 ? later[1] : later[0]);
+            const int mark = max(max(later[0], later[1]), max(later[2], later[3]));   // one for the block
             if (sub == 0 && i < a.n)
                 force[i] = f32x4{prev[0] + fx, prev[1] + fy, prev[2] + fz, (float)mark};
             fx = fy = fz = 0.f;
@@ -305,14 +309,20 @@ __global__ void __launch_bounds__(256) md_packed_kernel(MdPackedArgs s)
     }
 }
 
-const void *md_sort_kernel_table(int v)
+// 8 lanes; 16 with two loads for rows that are not read 4 indices at a time.
+const void *md_sort_kernel_table(int lanes, int v, int unroll)
 {
-    switch (v) {
-    case 1: return reinterpret_cast<const void *>(&md_kernel<8, 1, 4, true>);
-    case 2: return reinterpret_cast<const void *>(&md_kernel<8, 2, 4, true>);
-    case 4: return reinterpret_cast<const void *>(&md_kernel<8, 4, 4, true>);
-    default: return nullptr;
-    }
+    if (v == 4 && lanes == 8)
+        switch (unroll) {
+        case 2: return reinterpret_cast<const void *>(&md_kernel<8, 4, 2, true>);
+        case 4: return reinterpret_cast<const void *>(&md_kernel<8, 4, 4, true>);
+        }
+    if (lanes == 16 && unroll == 2)
+        switch (v) {
+        case 1: return reinterpret_cast<const void *>(&md_kernel<16, 1, 2, true>);
+        case 2: return reinterpret_cast<const void *>(&md_kernel<16, 2, 2, true>);
+        }
+    return nullptr;
 }
 
 const void *md_packed_kernel_table(int v)
