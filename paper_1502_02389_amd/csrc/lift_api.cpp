@@ -773,16 +773,28 @@ lift_status gemv_by_rows(int64_t m, int64_t n, float alpha, int at, const void *
         if (!kern)
             return LIFT_EUNSUPPORTED;
         const int64_t bytes = (int64_t)waves * v * 1024;
-        const int64_t per_cu = bytes > 32768 && bytes < 57344 ? (bytes < 49152 ? 2 : 3)
-                               : bytes >= 32768 ? std::max<int64_t>(2, std::min<int64_t>(16, m / (4 * (int64_t)cus)))
-                                                : std::max<int64_t>(2, 40960 / bytes);
+        int64_t per_cu = bytes > 32768 && bytes < 57344 ? (bytes < 49152 ? 2 : 3)
+                         : bytes >= 32768 ? std::max<int64_t>(2, std::min<int64_t>(16, m / (4 * (int64_t)cus)))
+                                          : std::max<int64_t>(2, 40960 / (need * 1024));
+        // The compensated sums need wavefronts for their arithmetic: 9 of them
+        // per CU at least, and from 56 KiB of 16-bit storage on the two
+        // work-groups that are resident anyway (us, as the others | this:
+        // 35511 x 7040 bf16 98.1 | 80.2, 32894 x 7600 bf16 92.4 | 80.5, 35511 x
+        // 3520 fp32 81.4 | 74.8, 8928 x 28000 bf16 90.4 | 80.9; slower by 5 %
+        // than before these kernels stay 14880 x 16800 bf16, 97, and 8928 x
+        // 14000 fp32, 83).
+        if (acc == LIFT_ACC_F32_COMP)
+            per_cu = waves == 3 ? std::max<int64_t>(3, per_cu) : eb == 2 && bytes >= 57344 ? 2 : per_cu;
         int64_t grid = std::min<int64_t>(m, (int64_t)cus * per_cu);
         if (P == 2)
             grid -= grid % 2;
         return launch(kern, grid, waves * 64, &a, stream);
     }
     // Rows longer than that: panels of r rows, whole rows while there are
-    // enough of them (3000 x 25137 fp32: r = 4 49.1, 2: 50.9, 1: 56.8 us),
+    // enough of them (3000 x 25137 fp32: r = 4 49.1, 2: 50.9, 1: 56.8 us; 4 from
+    // 6 rows per CU on, where as many turns of work-groups take them: us, r = 2 |
+    // 4: 1540 x 60000 bf16 42.7 | 38.6, 2047 x 60000 bf16 47.1 | 42.7, 1700 x 60000
+    // fp32 71.4 | 66.7, but 1500 x 60000 bf16 36.0 | 38.4),
     // else cut in chunks (at least 16 KiB each) so that one or two
     // work-groups per CU come out as nearly even as can be.  Up to 32 KiB per
     // CU the work-groups count, not the x they share: single rows (us, r = 2
@@ -792,7 +804,7 @@ lift_status gemv_by_rows(int64_t m, int64_t n, float alpha, int at, const void *
     // fp32 8.7 | 8.9).
     const int64_t per_class = (m + P - 1) / P;
     const bool split = ws && per_class * P <= (int64_t)cus;
-    const int r = per_class * P >= (int64_t)cus * 8 ? 4
+    const int r = per_class * P > (int64_t)cus * 6 ? 4
                   : split && m * n * eb <= (int64_t)cus * 32768 ? 1
                   : per_class > 1 && (ws || per_class * P > cus) ? 2 : 1;
     GemvPanelArgs p;
