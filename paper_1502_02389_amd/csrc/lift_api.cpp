@@ -1800,10 +1800,15 @@ lift_status lift_scal_ex(int64_t n, float alpha, const float *x, float *out, con
     // alignment: the shortest chain of a load and a store, and the most
     // work-groups (replayed from a graph, us, with 8 dwords per thread | this:
     // 2^20 3.25 | 2.84, 3000001 7.2 | 5.4, 2^21 4.06 | 3.82, 2^22 6.85 | 6.86,
-    // 2^23 12.18 | 12.28).
+    // 2^23 12.18 | 12.28).  Else, from 4 to 8 MiB, 4 dwords (8 | 4: 1100000 3.31 |
+    // 3.12, 2000000 5.60 | 4.44; but 1000000 3.55 | 3.67, 2108370 5.39 | 5.99).
     Split3 sp;
-    const bool wide = !knobs && n <= 1 << 22 && n > 0 && split3(x, out, n, 4, 16, &sp);
-    st = resolve(knobs, wide ? Knobs{256, 16, 1, 1, 0, 32, 1, 1, 0} : DEF_SCAL, 4, &k);
+    Knobs def = DEF_SCAL;
+    if (!knobs && n > 0 && n <= 1 << 22 && split3(x, out, n, 4, 16, &sp))
+        def = {256, 16, 1, 1, 0, 32, 1, 1, 0};
+    else if (!knobs && n >= 1 << 20 && n < 1 << 21)
+        def.unroll = 4;
+    st = resolve(knobs, def, 4, &k);
     if (st != LIFT_OK)
         return st;
     if (k.vec_bytes < 4)
