@@ -620,6 +620,8 @@ lift_status reduce_common(int op, int64_t n, int xt, const void *x, const void *
             k = {512, 16, 2, 1, 0, 1, 1, 1, 1, 0};
         vb = shifted ? 16 : eb;
         split3(x, nullptr, n, eb, vb, &sp);
+        while (shifted && k.block > 64 && sp.nvec <= k.block)   // half as many threads still take it in one step
+            k.block /= 2;
     }
     int cus = 0;
     // Only where the order of the binary32 sums does not matter beyond the last
