@@ -413,19 +413,18 @@ __global__ void __launch_bounds__(512) gemv_panel_kernel(GemvPanelArgs a)
             a.rows.y[r0 + t * P] = row_epilogue<ACC>(d, a.rows.alpha, a.rows.beta, yold);
         return;
     }
-    D v[R];
     unsigned *pending = reinterpret_cast<unsigned *>(a.ws + WS_GROUPS + group * WS_GROUP_STRIDE);
-    if (!meet<1>(a.ws, pending, group * a.chunks * R, a.chunks, chunk, d, a.rounds, v))
-        return;
-    D sum = zero_of<D>();
+    meet<1, D, R>(a.ws, pending, group * a.chunks * R, a.chunks, chunk, d, a.rounds, [&](D(&v)[R]) {
+        D sum = zero_of<D>();
 #pragma unroll
-    for (int i = 0; i < R; ++i) {
-        const D s = lanes_sum<64>(v[i]);
-        if (t == i)
-            sum = s;
-    }
-    if (row_lane)
-        a.rows.y[r0 + t * P] = row_epilogue<ACC>(sum, a.rows.alpha, a.rows.beta, yold);
+        for (int i = 0; i < R; ++i) {
+            const D s = lanes_sum<64>(v[i]);
+            if (t == i)
+                sum = s;
+        }
+        if (row_lane)
+            a.rows.y[r0 + t * P] = row_epilogue<ACC>(sum, a.rows.alpha, a.rows.beta, yold);
+    });
 }
 
 // Instances.  rows: (L, V) covering the row, R rows per group in flight.

@@ -400,10 +400,10 @@ __device__ __forceinline__ void fold_slots(char *ws, int64_t slot0, int64_t last
 
 // Where `count` (at least 2) work-groups meet: each calls meet() with one
 // wavefront, its `index`, and in lane i < R its partial of row i (the slots are
-// [row][index] from slot0 on).  True (wave-uniform) in exactly one of them,
-// which then holds in lane t of v[i] the fold of row i's partials t, t + 64,
+// [row][index] from slot0 on).  Exactly one of them, as a whole wavefront, then
+// calls finish(v), with lane t of v[i] the fold of row i's partials t, t + 64,
 // ... (LOADS of them in flight, twice as many where there are more rounds of
-// that), and has cleared the slots.
+// that), when it has cleared the slots.
 //
 // The last work-group waits for the others' partials, but not for good: which
 // work-groups run at the same time is the hardware's choice, and another
@@ -488,10 +488,11 @@ struct Meeting {
     }
 };
 
-template <int LOADS, class ST, int R>
-__device__ __forceinline__ bool meet(char *ws, unsigned *pending, int64_t slot0, int64_t count, int64_t index, ST own,
-                                     int rounds, ST (&v)[R])
+template <int LOADS, class ST, int R, class F>
+__device__ __forceinline__ void meet(char *ws, unsigned *pending, int64_t slot0, int64_t count, int64_t index, ST own,
+                                     int rounds, F &&finish)
 {
+    ST v[R];
     Meeting<ST, R> m{ws, pending, slot0, count, index, own, v};
     const int t = threadIdx.x & 63;
     unsigned marks = 0;
@@ -502,17 +503,22 @@ __device__ __forceinline__ bool meet(char *ws, unsigned *pending, int64_t slot0,
                                            __HIP_MEMORY_SCOPE_AGENT) == SLOT_MARK;
         marks = __popcll(__ballot(marked));
         if (__builtin_expect(marks == 0, 1))
-            return false;
+            return;
     } else {
-        bool all;
-        if constexpr (LOADS == 1)
-            all = m.template fold<1>(rounds);
-        else
-            all = count <= 64 * LOADS ? m.template fold<LOADS>(rounds) : m.template fold<2 * LOADS>(rounds);
-        if (__builtin_expect(all, 1))
-            return true;
+        // the common case's code follows at once: what lies in between costs a
+        // miss of the instruction cache each (0.1 us)
+        if (__builtin_expect(LOADS == 1 || count <= 64 * LOADS, 1)) {
+            if (__builtin_expect(m.template fold<LOADS>(rounds), 1)) {
+                finish(v);
+                return;
+            }
+        } else if (__builtin_expect(m.template fold<2 * LOADS>(rounds), 1)) {
+            finish(v);
+            return;
+        }
     }
-    return m.hand_over(marks);
+    if (m.hand_over(marks))
+        finish(v);
 }
 
 // The work-group's partial wg (valid in thread 0; every thread calls this
@@ -555,18 +561,17 @@ __device__ __forceinline__ void combine_partials(const ReduceArgs &a, W wg)
         stamp_arrival<STAMP>(a, 0);
 
     // the final reduce-seq o join, by one wavefront
-    ST v[1];
-    if (!meet<4>(ws, pending, 0, count, blockIdx.x, ST(wg), a.rounds, v))
-        return;
-    const ST total = wave_sum(v[0]);
-    if (t == 0)
-        write_result(a.result, a.result_f64, total);
-    if constexpr (STAMP) {
+    meet<4, ST, 1>(ws, pending, 0, count, blockIdx.x, ST(wg), a.rounds, [&](ST(&v)[1]) {
+        const ST total = wave_sum(v[0]);
         if (t == 0)
-            a.stamps[(int64_t)blockIdx.x * STAMPS_PER_WG + 6] |= 1ull << 32;
-        __builtin_amdgcn_sched_barrier(0);
-        stamp<STAMP>(a, 5);
-    }
+            write_result(a.result, a.result_f64, total);
+        if constexpr (STAMP) {
+            if (t == 0)
+                a.stamps[(int64_t)blockIdx.x * STAMPS_PER_WG + 6] |= 1ull << 32;
+            __builtin_amdgcn_sched_barrier(0);
+            stamp<STAMP>(a, 5);
+        }
+    });
 }
 
 // SHIFTED (dot, 16-byte vectors): y does not share x's 16-byte phase and is
