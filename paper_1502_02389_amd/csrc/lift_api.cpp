@@ -1689,18 +1689,24 @@ struct OutsideCapture {
     ~OutsideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
 
-// Zeros in mem, on a stream of its own, when this returns.
-hipError_t zero_now(void *mem, size_t bytes)
+// Zeros in mem, memory of the current device, when this returns: on a stream
+// that is kept per device (making one for each capture takes 0.4 ms).
+hipError_t zero_now(void *mem, size_t bytes, int dev)
 {
-    hipStream_t side = nullptr;
-    hipError_t e = hipStreamCreateWithFlags(&side, hipStreamNonBlocking);
-    if (e != hipSuccess)
-        return e;
-    e = hipMemsetAsync(mem, 0, bytes, side);
-    if (e == hipSuccess)
-        e = hipStreamSynchronize(side);
-    (void)hipStreamDestroy(side);
-    return e;
+    static std::atomic<hipStream_t> sides[MAX_DEVICES];
+    hipStream_t side = sides[dev].load(std::memory_order_acquire);
+    if (!side) {
+        hipStream_t made = nullptr;
+        const hipError_t e = hipStreamCreateWithFlags(&made, hipStreamNonBlocking);
+        if (e != hipSuccess)
+            return e;
+        if (sides[dev].compare_exchange_strong(side, made))
+            side = made;
+        else
+            (void)hipStreamDestroy(made);   // another thread was first
+    }
+    const hipError_t e = hipMemsetAsync(mem, 0, bytes, side);
+    return e == hipSuccess ? hipStreamSynchronize(side) : e;
 }
 
 lift_status capture_workspace(hipStream_t stream, void **ws)
@@ -1717,6 +1723,8 @@ lift_status capture_workspace(hipStream_t stream, void **ws)
     e = hipGetDevice(&dev);
     if (e != hipSuccess)
         return hip_fail(e);
+    if (dev < 0 || dev >= MAX_DEVICES)
+        return LIFT_EUNSUPPORTED;
     GraphWorkspaces &all = graph_workspaces();
     GraphWorkspace *mine = nullptr;
     std::vector<GraphWorkspace *> over;
@@ -1749,7 +1757,7 @@ lift_status capture_workspace(hipStream_t stream, void **ws)
         e = hipMalloc(&mine->mem, lift_workspace_bytes());
     }
     if (e == hipSuccess)
-        e = zero_now(mine->mem, lift_workspace_bytes());
+        e = zero_now(mine->mem, lift_workspace_bytes(), dev);
     if (e != hipSuccess) {
         (void)hipFree(mine->mem);
         delete mine;
