@@ -1115,6 +1115,44 @@ lift_status batch_wave_groups(int storage, int acc, const void **kern, int64_t *
     return st;
 }
 
+// How a wavefront takes the rows of a gemv tile (wave_gemv): `rows` of them in
+// `steps` rounds of loads.
+struct WaveRows {
+    int64_t rows, steps;
+};
+
+WaveRows wave_rows_step(int64_t n, int64_t eb, int acc)
+{
+    const int64_t vecs = (n * eb + 15) / 16;
+    if (vecs <= 64) {
+        int64_t lanes = 8;
+        while (lanes < 64 && lanes < vecs)
+            lanes *= 2;
+        return {4 * 64 / lanes, 1};
+    }
+    if (vecs <= 128 || (vecs <= 192 && eb == 4))
+        return {2, 1};
+    if (vecs <= 448 && (vecs <= 384 || eb == 4 || acc != LIFT_ACC_F32_COMP))
+        return {1, 1};
+    if ((vecs <= 512 && (eb == 4 || acc != LIFT_ACC_F32_COMP)) || (vecs <= 1024 && eb == 4 && acc == LIFT_ACC_F32))
+        return {1, (vecs + 255) / 256};
+    return {2, (vecs + 255) / 256};
+}
+
+// What a wavefront's rounds of loads cost, in bytes: one that moves less than
+// 8 KiB takes no less time.
+constexpr int64_t WAVE_STEP = 8192;
+
+// A problem's share of a batch of wavefront tiles, in such bytes (a gemv row's,
+// or the whole reduction's).
+double wave_cost(const lift_problem &q, int64_t eb, int acc)
+{
+    if (q.kind != LIFT_KIND_GEMV)
+        return std::max<double>(WAVE_STEP, (double)q.n * eb * (q.kind == LIFT_KIND_DOT ? 2 : 1));
+    const WaveRows w = wave_rows_step(q.n, eb, acc);
+    return std::max<double>((double)q.n * eb, (double)w.steps * WAVE_STEP / w.rows);
+}
+
 // Bytes of x, y and A that a batch reads, and the problems that read any.
 double batch_reads(const lift_problem *probs, int32_t count, int64_t eb, int64_t *filled)
 {
@@ -1168,9 +1206,9 @@ bool batch_choose(const lift_problem *probs, int32_t count, int storage, int acc
 // The plan of a batch without knobs (lift_batch_wave.hpp), its problems
 // already checked.
 //
-// Tile size (bytes of x, y and A): what gives every wavefront about one tile
-// (problems shorter than that leave more tiles than wavefronts, which are then
-// drawn).  Never below 8 KiB, one step of loads.
+// Tile size (in bytes as of wave_cost): what gives every wavefront about one
+// tile (problems shorter than that leave more tiles than wavefronts, which are
+// then drawn).  Never below one step of loads.
 lift_status batch_plan_waves(const lift_problem *probs, int32_t count, int storage, int acc, int rt, int64_t bytes,
                              lift_batch *b)
 {
@@ -1181,8 +1219,12 @@ lift_status batch_plan_waves(const lift_problem *probs, int32_t count, int stora
     if (st != LIFT_OK)
         return st;
     const int64_t waves = most * 4;
-    const double total = batch_reads(probs, count, eb, &filled);
-    const int64_t tile = (int64_t)std::max(8192.0, total / std::max<int64_t>(waves / 2, waves - filled));
+    double total = 0;
+    batch_reads(probs, count, eb, &filled);
+    for (int32_t i = 0; i < count; ++i)
+        total += wave_cost(probs[i], eb, acc) * (probs[i].kind == LIFT_KIND_GEMV ? (double)probs[i].m : 1);
+    const int64_t tile =
+        (int64_t)std::max<double>(WAVE_STEP, std::min(1e15, total / std::max<int64_t>(waves / 2, waves - filled)));
 
     // Equal tiles of one problem, one after the other: a, b and out advance by
     // these many bytes, a reduction's slot and its number in its problem by 1.
@@ -1193,6 +1235,7 @@ lift_status batch_plan_waves(const lift_problem *probs, int32_t count, int stora
     std::vector<Run> runs;
     runs.reserve(2 * (size_t)count);
     int64_t slots = 0, kinds[2] = {0, 0};
+    bool grouped = false;   // some reduction has more than TILE_GROUP tiles
     // `total` units in tiles of `unit`: a run of whole ones and the rest
     const auto cut = [&](Run r, int64_t total_units, int64_t unit, int32_t WaveTile::*length, int64_t unit_bytes) {
         const int64_t whole = total_units / unit, rest = total_units - whole * unit;
@@ -1233,14 +1276,12 @@ lift_status batch_plan_waves(const lift_problem *probs, int32_t count, int stora
                 continue;
             if (q.n > INT32_MAX)
                 return LIFT_EUNSUPPORTED;
-            // whole groups of the rows that a wavefront has in flight: 4 x 64 / L
-            // side by side for rows of L <= 64 vectors
-            const int64_t vecs = (q.n + e - 1) / e;
-            int64_t lanes = 8;
-            while (lanes < 64 && lanes < vecs)
-                lanes *= 2;
-            const int64_t unit = vecs <= 64 ? 4 * 64 / lanes : 4;
-            const int64_t want = std::max<int64_t>(unit, tile / std::max<int64_t>(1, q.n * eb));
+            // whole groups of the rows that a wavefront has in flight (pairs of
+            // long rows share x: single ones only where each is several tiles)
+            const WaveRows w = wave_rows_step(q.n, eb, acc);
+            const double cost = wave_cost(q, eb, acc);
+            const int64_t unit = w.rows == 2 && w.steps > 1 && cost > 4 * (double)tile ? 1 : w.rows;
+            const int64_t want = std::max<int64_t>(unit, (int64_t)std::ceil((double)tile / cost));
             const int64_t nt = (q.m + want - 1) / want;
             int64_t rows = (q.m + nt - 1) / nt;
             rows = std::min<int64_t>((rows + unit - 1) / unit * unit, 1 << 30);
@@ -1251,7 +1292,7 @@ lift_status batch_plan_waves(const lift_problem *probs, int32_t count, int stora
             r.t.ntiles = 1;
             r.da = rows * q.lda * eb;
             r.dout = rows * 4;
-            cut(r, q.m, rows, &WaveTile::rows, q.n * eb);
+            cut(r, q.m, rows, &WaveTile::rows, (int64_t)cost);
         } else {
             const int64_t streams = q.kind == LIFT_KIND_DOT ? 2 : 1;
             const int64_t want = std::max<int64_t>(64 * e, tile / (eb * streams));
@@ -1259,6 +1300,9 @@ lift_status batch_plan_waves(const lift_problem *probs, int32_t count, int stora
             int64_t len = (q.n + nt - 1) / nt;
             len = std::min<int64_t>(std::max<int64_t>(64 * e, (len + 64 * e - 1) / (64 * e) * (64 * e)), 1 << 30);
             nt = std::max<int64_t>(1, (q.n + len - 1) / len);
+            grouped |= nt > TILE_GROUP;
+            if (nt > TILE_GROUP)
+                slots = (slots + TILE_GROUP - 1) / TILE_GROUP * TILE_GROUP;
             if (slots + nt > INT32_MAX)
                 return LIFT_EUNSUPPORTED;
             r.t.a = q.n ? q.a : nullptr;
@@ -1281,12 +1325,13 @@ lift_status batch_plan_waves(const lift_problem *probs, int32_t count, int stora
     if (he != hipSuccess)
         return hip_fail(he);
     // one allocation: draw counters | counter and groups of work-groups that
-    // left | per-problem counters | tiles | records | slots; all but the slots
-    // in one upload
+    // left | per-problem counters | counters of groups of tiles | tiles | records
+    // | slots; all but the slots in one upload
     auto up = [](int64_t v) { return (v + 255) / 256 * 256; };
     const int64_t off_done = up(DRAW_LISTS * WS_GROUP_STRIDE), off_groups = off_done + 256;
     const int64_t off_pc = off_groups + up((grid + ARRIVAL_GROUP - 1) / ARRIVAL_GROUP * WS_GROUP_STRIDE);
-    const int64_t off_ti = off_pc + up(std::max<int64_t>(count, 1) * 4);
+    const int64_t off_gc = off_pc + up(std::max<int64_t>(count, 1) * 4);
+    const int64_t off_ti = off_gc + (grouped ? up((slots / TILE_GROUP + 1) * WS_GROUP_STRIDE) : 0);
     const int64_t off_re = off_ti + up(std::max<int64_t>(ntiles, 1) * (int64_t)sizeof(WaveTile));
     const int64_t off_sl = off_re + up(std::max<int64_t>(ntiles, 1) * 4);
     std::vector<char> image((size_t)off_sl);
@@ -1335,6 +1380,7 @@ lift_status batch_plan_waves(const lift_problem *probs, int32_t count, int stora
     a.done = reinterpret_cast<unsigned *>(base + off_done);
     a.groups = base + off_groups;
     a.pcount = reinterpret_cast<unsigned *>(base + off_pc);
+    a.gcount = base + off_gc;
     a.slots = base + off_sl;
     a.result_f64 = rt == LIFT_F64;
     a.dynamic = ntiles > grid * 4;

@@ -216,6 +216,7 @@ struct WaveTile {
 static_assert(sizeof(WaveTile) == 64, "the kernel reads it as 16 words");
 
 constexpr int DRAW_LISTS = 8;
+constexpr int32_t TILE_GROUP = 64;   // tiles of a reduction that are folded together
 
 struct BatchWaveArgs {
     const WaveTile *tiles;
@@ -223,8 +224,9 @@ struct BatchWaveArgs {
     char *lists;          // DRAW_LISTS counters of drawn tiles, WS_GROUP_STRIDE apart
     unsigned *done;       // groups of work-groups that have left (arrive())
     char *groups;
-    unsigned *pcount;     // per problem: tiles finished
-    char *slots;
+    unsigned *pcount;     // per problem: tiles, or groups of tiles, finished
+    char *gcount;         // tiles finished per group: of slots g * TILE_GROUP on, g * WS_GROUP_STRIDE
+    char *slots;          // a problem of more than TILE_GROUP tiles starts at a multiple of that
     int32_t result_f64;
     int32_t dynamic;      // more tiles than wavefronts: draw
     const int32_t *records;  // stamped instances: a tile's place in `stamps`
