@@ -13,6 +13,7 @@
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <new>
@@ -1334,9 +1335,10 @@ lift_status batch_plan_waves(const lift_problem *probs, int32_t count, int stora
     const int64_t off_ti = off_gc + (grouped ? up((slots / TILE_GROUP + 1) * WS_GROUP_STRIDE) : 0);
     const int64_t off_re = off_ti + up(std::max<int64_t>(ntiles, 1) * (int64_t)sizeof(WaveTile));
     const int64_t off_sl = off_re + up(std::max<int64_t>(ntiles, 1) * 4);
-    std::vector<char> image((size_t)off_sl);
-    WaveTile *table = reinterpret_cast<WaveTile *>(image.data() + off_ti);
-    int32_t *records = reinterpret_cast<int32_t *>(image.data() + off_re);   // stamps: reductions first, then gemv
+    const std::unique_ptr<char[]> image(new char[(size_t)off_sl]);
+    std::memset(image.get(), 0, (size_t)off_ti);
+    WaveTile *table = reinterpret_cast<WaveTile *>(image.get() + off_ti);
+    int32_t *records = reinterpret_cast<int32_t *>(image.get() + off_re);   // stamps: reductions first, then gemv
     int64_t at[2] = {0, kinds[0]};
     for (const Run &r : runs) {
         WaveTile w = r.t;
@@ -1357,7 +1359,7 @@ lift_status batch_plan_waves(const lift_problem *probs, int32_t count, int stora
     if (he != hipSuccess)
         return hip_fail(he);
     char *base = static_cast<char *>(mem);
-    if ((he = hipMemcpy(base, image.data(), image.size(), hipMemcpyHostToDevice)) != hipSuccess) {
+    if ((he = hipMemcpy(base, image.get(), (size_t)off_sl, hipMemcpyHostToDevice)) != hipSuccess) {
         hipFree(mem);
         return hip_fail(he);
     }
