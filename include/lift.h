@@ -296,7 +296,8 @@ lift_status lift_gemv_ex(int64_t m, int64_t n, float alpha, lift_dtype at, const
  * overlapping y).  With few, long rows (rows above 64 KiB, at most one row
  * or pair of rows per compute unit) the library then splits each row over
  * several work-groups, whose partials meet in the workspace in a fixed
- * order; every other shape runs as lift_gemv_ex. */
+ * order (another than lift_gemv_ex's: the last bits may differ); every other
+ * shape runs as lift_gemv_ex. */
 lift_status lift_gemv_ex_ws(int64_t m, int64_t n, float alpha, lift_dtype at, const void *A,
                             int64_t lda, const float *x, float beta, float *y, lift_acc acc, void *ws,
                             size_t ws_bytes, const lift_knobs *knobs, hipStream_t stream);
@@ -347,9 +348,10 @@ lift_status lift_blackscholes_ex(int64_t n, const float *s, float strike, float 
  * Binary32 throughout;
  * the sum over a list is split over the lanes given by lanes_per_item, in a
  * fixed order (deterministic).  Without knobs, systems of 2 to 4 times 5 MB of
- * positions with lists of at least 96 (2) or 64 slots run as several launches (an armed timing hook spans them): the
- * particles whose neighbours' indices are far from their own are summed a
- * slice of positions at a time, `force` holding the sums so far.  LIFT_EINVAL for bad sizes, pointers or
+ * positions with lists of at least 96 (2) or 64 slots run as several launches
+ * (an armed timing hook spans them): the particles most of whose neighbours'
+ * indices are far from their own are summed a slice of positions at a time,
+ * `force` holding the sums so far.  LIFT_EINVAL for bad sizes, pointers or
  * parameters; n must be below 2^31, and n * lanes_per_item (one thread per
  * lane of each particle) below 2^32: with the default 16 lanes, n below
  * about 2^28. */

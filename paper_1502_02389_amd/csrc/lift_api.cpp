@@ -743,9 +743,9 @@ lift_status gemv_by_rows(int64_t m, int64_t n, float alpha, int at, const void *
         if (!kern)
             return LIFT_EUNSUPPORTED;
         // 8 work-groups per CU; 2 where a lane has more than one vector per
-        // row and so 6 to 8 loads in flight by itself (4096 x 4096 bf16: 8.1
-        // against 9.4, 16384 x 1000 bf16: 7.5 against 7.7, but 1000000 x 33
-        // fp32: 22.2 against 21.6 us)
+        // row (5 to 8 loads in flight with several rows, 2 to 8 with one):
+        // 4096 x 4096 bf16 8.1 against 9.4, 16384 x 1000 bf16 7.5 against 7.7,
+        // but 1000000 x 33 fp32 22.2 against 21.6 us
         const int64_t grid = std::min<int64_t>((units + 3) / 4, (int64_t)cus * (v > 1 ? 2 : 8));
         return launch(kern, grid, 256, &a, stream);
     }
@@ -759,7 +759,7 @@ lift_status gemv_by_rows(int64_t m, int64_t n, float alpha, int at, const void *
         // work-groups (16384 x 8191 fp32: 16 per CU 80.3, 2 per CU 82.8 us)
         // of at least 4 rows, each reading its part of x once (3000 x 25137
         // bf16: one row each 35.6, 2 work-groups per CU 27.9 us) -- but not
-        // between 32 and 56 KiB, where a work-group has 5 or 6 wavefronts, no
+        // between 32 and 56 KiB, where a work-group has 5 to 7 wavefronts, no
         // multiple of a CU's 4 SIMDs: 2 per CU, 3 from 48 KiB on (us, as the
         // others | this: 14000 x 9800 fp32 89.3 | 86.2, 13000 x 8400 fp32 70.0 |
         // 67.4, 13000 x 20000 bf16 84.7 | 82.2, 7900 x 12000 fp32 57.4 | 56.4,
@@ -1034,11 +1034,11 @@ lift_status stream_common(bool copy, int64_t n, const float *x, float *out, cons
 
 // ---- allocation-free reductions --------------------------------------------
 //
-// lift_dot_ex_noalloc keeps its arrival counters and partial slots in this
-// file-scope device array instead of a caller workspace: one copy per device,
-// zero-filled when the library's code object is loaded on it, and left with
-// its counters zeroed by every call that completes (the last work-group
-// resets them), so nothing is cleared per call.  In host code `scratch` names
+// lift_dot_ex_noalloc keeps its counters and partial slots in this file-scope
+// device array instead of a caller workspace: one copy per device, zero-filled
+// when the library's code object is loaded on it, and left as the next call
+// needs it by every call (the work-group that combines clears the slots and
+// counters that were used), so nothing is cleared per call.  In host code `scratch` names
 // a host-side stand-in; the device address of each device's copy comes from
 // hipGetSymbolAddress with that device current, once, and only that address
 // is handed to kernels.

@@ -274,7 +274,7 @@ __device__ __forceinline__ void wave_long_rows(const WaveTile &t, int lane)
 
 // A gemv tile by its row length (all wave-uniform).  Each instance takes the
 // rows that the one before does not cover, so all but the last of its lanes'
-// vectors are whole (or the WHOLE that it names), and keeps 4 to 8 loads in
+// vectors are whole (or the WHOLE that it names), and keeps 3 to 8 loads in
 // flight.
 template <class T, int ACC>
 __device__ __forceinline__ void wave_gemv(const WaveTile &t, int lane)

@@ -15,7 +15,7 @@
 // All of them read 16 bytes per lane from wherever a row starts.  gfx950
 // serves a 16-byte load at any 4-byte boundary at the full streaming rate
 // (512 MiB flat read: 74.4-75.0 us at byte offsets 0, 4, 8, 12) and at an odd
-// 2-byte boundary a quarter slower (100.5-101.0 us), so only 16-bit rows that
+// 2-byte boundary in 35 % more time (100.5-101.0 us), so only 16-bit rows that
 // start between two dwords need anything: their first column is taken as a
 // scalar head and the vectors start at the second.  With an odd pitch every
 // other row is such a row; the rows are dealt so that a lane only ever meets

@@ -444,10 +444,11 @@ def _zeros_outside_capture(nbytes, device):
 def _call_workspace(device, stream):
     """(address, bytes) of the workspace of a call on `stream`, the current
     stream of `device`: the graph's own where it is being captured."""
-    st, at = lift_capture_workspace(stream)
-    _ok(st, "lift_capture_workspace")
-    if at:
-        return at, lift_workspace_bytes()
+    if stream:                       # the null stream cannot be captured
+        st, at = lift_capture_workspace(stream)
+        _ok(st, "lift_capture_workspace")
+        if at:
+            return at, lift_workspace_bytes()
     ws = workspace(device)
     return ws.data_ptr(), ws.numel()
 
@@ -633,8 +634,9 @@ def gemv(alpha, A, x, beta, y, acc="f32", knobs=None, lda=None):
 
 
 class Batch:
-    """Many asum / dot / gemv problems run as two persistent kernels (reduction
-    tiles, then gemv tiles) on one stream.
+    """Many asum / dot / gemv problems planned once and run together on one
+    stream: as one persistent kernel of wavefront tiles, or, larger ones and
+    those with knobs, as two (reduction tiles, then gemv tiles).
 
     ``problems`` is a list of tuples:
       ("asum", x)                       -> result written to a 0-d tensor
